@@ -110,6 +110,19 @@ __device__ __forceinline__ SplitPlan attn_balanced_plan(const AttnArgs& a, int r
   const int cnt = (n + lo - 1) / lo;
   return SplitPlan{cnt, __ockl_wfscan_add_i32(cnt, true), lo};
 }
+// Sequence, row block, query tokens, first position and first activation row of a unit:
+// an entry of the block list (prompt passes, one split) or (sequence, row block).
+struct UnitInfo { int s, rb, nq, P, row0; };
+template <bool PROMPT>
+__device__ __forceinline__ UnitInfo attn_unit(const AttnArgs& a, int unit) {
+  if (PROMPT && a.blocks) {
+    const int32_t* b = a.blocks + (size_t)unit * kAttnBlockInts;
+    return UnitInfo{b[0], b[4], b[2], b[3], b[1]};
+  }
+  const int s = unit / a.row_blocks;
+  return UnitInfo{s, unit % a.row_blocks, a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq, a.pos0[s * a.seq_stride],
+                  s * a.rows_per_seq};
+}
 // Work of the workgroup at (blockIdx.x, blockIdx.z): unit, split index within the unit
 // and the unit's split count; false for a slot the balanced plan leaves idle.
 __device__ __forceinline__ bool attn_slot_work(const AttnArgs& a, int rbr, int& unit, int& split, int& nsplit) {
@@ -201,10 +214,9 @@ __global__ __launch_bounds__(256) void attn_staged_kernel(AttnArgs a) {
   const int kvh = blockIdx.y;
   int unit, split, nsplit;
   if (!attn_slot_work(a, kAttnRows, unit, split, nsplit)) return;
-  const int s = unit / a.row_blocks, rb = unit % a.row_blocks;
+  const UnitInfo ui = attn_unit<true>(a, unit);
+  const int s = ui.s, rb = ui.rb, nq = ui.nq, P = ui.P;
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
-  const int P = a.pos0[s * a.seq_stride];
   const int nrows = nq * G;                      // valid (token, head) rows of this sequence
   const int row0 = rb * kAttnRows;               // first row of this workgroup
   if (row0 >= nrows) return;
@@ -230,7 +242,7 @@ __global__ __launch_bounds__(256) void attn_staged_kernel(AttnArgs a) {
   {
     const int r = min(qrow, nrows - 1);
     const int tok = r / G, h = kvh * G + r % G;
-    const T* qp = (const T*)a.q + (size_t)(s * a.rows_per_seq + tok) * a.n_q_heads * HD + (size_t)h * HD;
+    const T* qp = (const T*)a.q + (size_t)(ui.row0 + tok) * a.n_q_heads * HD + (size_t)h * HD;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) qf[ks].load(qp + ks * 32 + g4 * 8);
   }
@@ -378,7 +390,7 @@ __global__ __launch_bounds__(256) void attn_staged_kernel(AttnArgs a) {
       const int tok = qrow / G, h = kvh * G + qrow % G;
       const float inv = lrun > 0.f ? 1.f / lrun : 0.f;
       T* op = (T*)a.out;
-      const int orow = s * a.rows_per_seq + tok;
+      const int orow = ui.row0 + tok;
 #pragma unroll
       for (int t = 0; t < NHT; ++t)
 #pragma unroll
@@ -536,6 +548,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
   constexpr int RH = 16 * NRT;                 // rows per wave
   constexpr int RBR = NW / 2 * RH;             // rows per workgroup (row block)
   constexpr int MERGE = RBR * OPITCH * 4 + RBR * 2 * 4;
+  constexpr bool PROMPT = NRT == 2;            // prompt passes: the only launches with two query tiles
   // copies per chunk: with four waves each copies one K and one V page; with eight or
   // more, waves 0-3 copy the K pages and waves 4-7 the V pages (the rest copy nothing)
   constexpr bool SPREAD = NW >= 8;
@@ -574,7 +587,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
   SpanPlan sp{};
   unsigned long long seg_units = 0;   // spanning: units still to run
   const int slot = blockIdx.z * a.splits + blockIdx.x;
-  if constexpr (!FUSED) {
+  if constexpr (!FUSED && !PROMPT) {
     if (a.span && attn_balanced(a)) {
       // span when its slots are shorter than the balanced plan's longest split by more
       // than the pipeline fill of a second segment (about three chunks, measured)
@@ -590,6 +603,8 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
     }
     seg_units = __ballot(sp.count > 0 && slot >= sp.first && slot < sp.first + sp.count);
     if (seg_units == 0) return;
+  } else if (PROMPT) {
+    unit = blockIdx.z;
   } else if (!attn_slot_work(a, RBR, unit, split, nsplit)) {
     return;
   }
@@ -610,10 +625,9 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
     part_blk = (size_t)kvh * attn_head_blocks(a) + (__builtin_amdgcn_readlane(sp.seg_end, unit) - nsplit) + split;
   }
   {
-  const int s = unit / a.row_blocks, rb = unit % a.row_blocks;
+  const UnitInfo ui = attn_unit<PROMPT>(a, unit);
+  const int s = ui.s, rb = ui.rb, nq = ui.nq, P = ui.P;
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
-  const int P = a.pos0[s * a.seq_stride];
   const int nrows = nq * G;
   const int row0 = rb * RBR;
   if (row0 >= nrows) goto seg_done;
@@ -647,7 +661,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
   }
   // with one row block per sequence every K / V chunk is read by one workgroup:
   // non-temporal copies (several row blocks, as in prefill, share the chunks through cache)
-  const bool stream_kv = a.row_blocks == 1;
+  const bool stream_kv = !PROMPT && a.row_blocks == 1;
   // With SPREAD a copying wave copies one page of K or one of V: its cache, per-lane
   // offsets and LDS slice are chosen once here, so that a chunk's copies cost one branch
   // and one page address.  stg_off: the byte offset of the stage.
@@ -713,7 +727,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
       load_frag_u<NKP>(cs, g4, qcs[t2]);
       load_frag_u<NKP>(cs + (size_t)a.rope_max_pos * (HD / 2), g4, qsn[t2]);
     } else {
-      const bf16_t* qp = (const bf16_t*)a.q + (size_t)(s * a.rows_per_seq + tok) * a.n_q_heads * HD + (size_t)h * HD;
+      const bf16_t* qp = (const bf16_t*)a.q + (size_t)(ui.row0 + tok) * a.n_q_heads * HD + (size_t)h * HD;
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) qf[t2][ks].load(qp + ks * 32 + g4 * 8);
     }
@@ -1104,7 +1118,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
         const int tok = qrow / G, h = kvh * G + qrow % G;
         const float inv = L > 0.f ? 1.f / L : 0.f;
         bf16_t* op = (bf16_t*)a.out;
-        const int orow = s * a.rows_per_seq + tok;
+        const int orow = ui.row0 + tok;
 #pragma unroll
         for (int t = 0; t < NHT; ++t)
 #pragma unroll
@@ -1212,12 +1226,20 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // merge is written in explicit fused form).
 template <typename T>
 hipError_t attention_partials(const AttnArgs& a, hipStream_t s) {
-  dim3 grid(a.splits, a.n_kv_heads, a.n_seqs * a.row_blocks);
+  if (a.blocks && (a.splits != 1 || a.qkv || a.n_blocks < 1)) return hipErrorInvalidValue;
+  dim3 grid(a.splits, a.n_kv_heads, a.blocks ? a.n_blocks : a.n_seqs * a.row_blocks);
   // the fused q / k post-processing: bf16 kernels, blocks of at most 16 rows per sequence
   if (a.qkv && (sizeof(T) != 2 || a.rows_per_seq > 16 || a.nq)) return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 2) {
     const bool f = a.qkv != nullptr;
-    if (a.rb_rows == 96) {
+    if (a.rb_rows == kAttnRowsPrompt) {
+      // prompt passes: two query tiles per wave, so that each K / V fragment read from LDS
+      // serves 32 query rows
+      if (!a.blocks) return hipErrorInvalidValue;
+      if (a.head_dim == 128) RT_LAUNCH((attn_bf16_kernel<128, 2, 2, 8, false>), grid, dim3(512), 0, s, a);
+      else if (a.head_dim == 64) RT_LAUNCH((attn_bf16_kernel<64, 2, 2, 8, false>), grid, dim3(512), 0, s, a);
+      else return hipErrorInvalidValue;
+    } else if (a.rb_rows == 96) {
       if (a.head_dim == 128 && f) RT_LAUNCH((attn_bf16_kernel<128, 3, 1, 12, true>), grid, dim3(768), 0, s, a);
       else if (a.head_dim == 128) RT_LAUNCH((attn_bf16_kernel<128, 3, 1, 12, false>), grid, dim3(768), 0, s, a);
       else if (a.head_dim == 64 && f) RT_LAUNCH((attn_bf16_kernel<64, 3, 1, 12, true>), grid, dim3(768), 0, s, a);

@@ -4,6 +4,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -241,9 +242,9 @@ struct Engine : EngineBase {
     const int shape = skinny ? SHAPE_SKINNY : SHAPE_WIDE;
     const int KT = Kp / 32;
     int ks = 1;
-    // bf16 GEMMs of 33..512 rows go to the mid-size kernel (which picks its own k slabs);
+    // bf16 GEMMs of more rows go to the mid-size kernel (which picks its own k slabs);
     // the test hook (flags & 4) keeps them on the 128x128 split-k path instead
-    const bool mid = shape == SHAPE_WIDE && sizeof(T) == 2 && M <= 512 && !(flags & 4);
+    const bool mid = shape == SHAPE_WIDE && sizeof(T) == 2 && !(flags & 4);
     if (shape == SHAPE_WIDE && !mid) {
       const int tiles = ((N + 127) / 128) * ((M + 127) / 128);
       if (flags & 4) {                       // test hook: force a k split wherever possible
@@ -274,9 +275,9 @@ struct Engine : EngineBase {
   }
 
   // k slabs of the q|k|v projection of M rows when it runs on the mid-size kernel
-  // (bf16, 65..512 rows; the test hook keeps the wide path), else 1
+  // (bf16, more than 64 rows; the test hook keeps the wide path), else 1
   int qkv_slabs(int M) const {
-    if (sizeof(T) != 2 || (flags & 4) || M <= 64 || M > 512) return 1;
+    if (sizeof(T) != 2 || (flags & 4) || M <= 64) return 1;
     GemmArgs g{};
     g.Kp = p.Kp_d; g.partial_floats = kPartialFloats;
     g.e.kind = EPI_STORE_F32; g.e.M = M; g.e.N = p.qkvN;
@@ -295,6 +296,12 @@ struct Engine : EngineBase {
     const int32_t* prof_ctx;     // host copy of each sequence's context length (profiling only)
     int defer;                   // o / down (<= 32 rows): k-slab partials, added by the next norm
     int trace = -1;              // layer-trace record of this layer (-1: none)
+    // prompt pass: its attention blocks and page items (then rows_per_seq, n_seqs, stride,
+    // rb, pos0 and nq are unused)
+    const int32_t* blocks = nullptr;
+    int n_blocks = 0;
+    const int32_t* items = nullptr;
+    int n_items = 0;
   };
   // partials of the last deferred residual GEMM, consumed by the next norm of x
   NormFold pend{};
@@ -313,17 +320,23 @@ struct Engine : EngineBase {
                  bool capture) {
     const Plan& q = p;
     EpiArgs e{};
-    if (c.defer && c.M <= q.rpart_rows && (c.M <= 32 || (sizeof(T) == 2 && !(flags & 4)))) {
-      const size_t stride = (size_t)q.rpart_rows * q.d;
-      // skinny rows: 4 slabs; 65..512 rows (mid-size kernel): the slab count that fills
-      // the chip (e.g. 40 column tiles x 6 slabs at the 14B shape), at most 8
-      int ks = kResidSplits;
+    // skinny rows: 4 slabs; 65 rows or more (mid-size kernel): the slab count that fills
+    // the chip (e.g. 40 column tiles x 6 slabs at the 14B shape), at most 8; one slab (large
+    // prompt passes) adds to x in the epilogue instead.  Slabs are rpart_rows apart in
+    // rounds; prompt passes pack them.
+    const size_t stride = (size_t)(c.blocks ? c.M : q.rpart_rows) * q.d;
+    const bool defer = c.defer && (c.blocks || c.M <= q.rpart_rows) && (c.M <= 32 || (sizeof(T) == 2 && !(flags & 4)));
+    int ks = 1;
+    if (defer) {
+      ks = kResidSplits;
       if (c.M > 64 && sizeof(T) == 2) {
         GemmArgs g{};
-        g.Kp = Kp; g.partial_floats = (size_t)kResidSplitsMax * stride;
+        g.Kp = Kp; g.partial_floats = c.blocks ? q.rpart_floats : (size_t)kResidSplitsMax * stride;
         g.e.kind = EPI_PARTIAL; g.e.M = c.M; g.e.N = q.d;
         ks = gemm_mid_partial_slabs(g, false, kResidSplitsMax);
       }
+    }
+    if (defer && (ks > 1 || c.M <= 512)) {
       e.kind = EPI_PARTIAL; e.out_f32 = pat<float>(q.rpart, q.s_rpart); e.ldo = q.d; e.part_stride = stride;
       CHK(gemm_call(kind, A, lda, q.Mrows, false, W, q.d, Kp, c.M, e, k_logical, ks));
       pend = NormFold{pat<float>(q.rpart, q.s_rpart), ks, stride, capture ? (void*)c.cap : nullptr, 16 * q.Kp_nc,
@@ -355,7 +368,7 @@ struct Engine : EngineBase {
     // Rounds and target-only steps (at most 16 rows per sequence, bf16, one q|k|v slab):
     // the attention kernel does the q / k-norm, the rotation and the block's K / V cache
     // write itself (debug flag 16 keeps the separate kernel)
-    const bool fusable = sizeof(T) == 2 && qks == 1 && c.nq == nullptr && c.rows_per_seq <= 16 &&
+    const bool fusable = sizeof(T) == 2 && qks == 1 && !c.blocks && c.rows_per_seq <= 16 &&
                          (q.hd == 64 || q.hd == 128);
     const bool fuse = fusable && !(flags & 16);
     if (!fuse) {
@@ -370,7 +383,7 @@ struct Engine : EngineBase {
       qp.rope = at<float>(q.rope); qp.rope_max_pos = q.T; qp.eps = cfg.rms_eps;
       qp.rows_per_seq = c.rows_per_seq; qp.seq_stride = c.stride; qp.pos0 = c.pos0; qp.nrows = nullptr;
       prof_begin(RT_K_QKV_POST, (double)c.M * q.qkvN * (4 * qks + sizeof(T)), 0);
-      HIPCHK(qkv_post<T>(qp, stream));
+      HIPCHK(c.items ? qkv_post_pages<T>(qp, c.items, c.n_items, stream) : qkv_post<T>(qp, stream));
       prof_end();
       CHK(trace_item(c.trace, TI_Q, at<T>(q.qbuf)));
     }
@@ -379,6 +392,7 @@ struct Engine : EngineBase {
     a.pos0 = c.pos0; a.nq = c.nq; a.seq_stride = c.stride; a.rows_per_seq = c.rows_per_seq;
     a.n_seqs = c.n_seqs; a.causal = c.causal; a.n_q_heads = q.Hq; a.n_kv_heads = q.Hkv; a.head_dim = q.hd;
     a.splits = c.splits; a.row_blocks = c.rb; a.rb_rows = c.rb_rows;
+    a.blocks = c.blocks; a.n_blocks = c.n_blocks;
     // batches whose attention never takes the q / k work (so the fused and separate forms,
     // compared by a test hook, share one plan) may span unit boundaries
     a.span = fusable ? 0 : (flags & 64) ? 2 : 1;
@@ -426,7 +440,7 @@ struct Engine : EngineBase {
   // LM head over rows of xa with a fused argmax into keys[M] (optional fp32 logits).
   int lm_head_argmax(int M, uint64_t* keys, float* logits) {
     const Plan& q = p;
-    if (sizeof(T) == 2 && M > 32 && M <= 512) {   // mid-size rows: one pass over the vocabulary
+    if (sizeof(T) == 2 && M > 32) {   // mid-size rows: one pass over the vocabulary
       GemmArgs g{};
       g.A = at<T>(q.xa); g.lda = 16 * q.Kp_d; g.a_rows = q.Mrows; g.B = at<T>(q.lm_head); g.Kp = q.Kp_d; g.ksplit = 1;
       g.e.kind = EPI_ARGMAX; g.e.M = M; g.e.N = q.V; g.e.out_f32 = logits; g.e.ldo = q.V;
@@ -482,8 +496,9 @@ struct Engine : EngineBase {
   }
 
   // Drafter context pathway for M rows: fc -> RMSNorm -> per-layer K (k-norm, RoPE) / V.
+  // Prompt passes give the rows as page items instead of (pos0, nrows).
   int context_append(int M, int rows_per_seq, const int32_t* pos0, const int32_t* nrows, int stride,
-                     const int32_t* pt) {
+                     const int32_t* pt, const int32_t* items = nullptr, int n_items = 0) {
     const Plan& q = p;
     EpiArgs e{};
     e.kind = EPI_STORE_F32; e.out_f32 = at<float>(q.fcout); e.ldo = q.d;
@@ -505,7 +520,7 @@ struct Engine : EngineBase {
     qp.rope = at<float>(q.rope); qp.rope_max_pos = q.T; qp.eps = cfg.rms_eps;
     qp.rows_per_seq = rows_per_seq; qp.seq_stride = stride; qp.pos0 = pos0; qp.nrows = nrows;
     prof_begin(RT_K_QKV_POST, (double)M * q.LD * 2 * q.kvN * (4 + sizeof(T)), 0);
-    HIPCHK(qkv_post<T>(qp, stream));
+    HIPCHK(items ? qkv_post_pages<T>(qp, items, n_items, stream) : qkv_post<T>(qp, stream));
     prof_end();
     return RT_OK;
   }
@@ -587,45 +602,86 @@ struct Engine : EngineBase {
     return RT_OK;
   }
 
+  // Prompt tables of one prefill, as uploaded to pf_tab: the prompts' tokens laid end to
+  // end, each sequence's first token index (n_seqs + 1 offsets), and per pass the attention
+  // blocks and page items (int32 offsets into the table).
+  struct PromptPass { int g0, rows, first_end, n_end; size_t blocks, items; int n_blocks, n_items; };
+  struct PromptTables { std::vector<int32_t> tab; size_t off; std::vector<PromptPass> passes; };
+  void prompt_tables(int ns, const int32_t* lens, const int32_t* ids, PromptTables* out) const {
+    const Plan& q = p;
+    std::vector<int32_t> off(ns + 1, 0);
+    for (int s = 0; s < ns; ++s) off[s + 1] = off[s] + lens[s];
+    const int total = off[ns];
+    std::vector<int32_t>& t = out->tab;
+    t.assign(ids, ids + total);
+    out->off = t.size();
+    t.insert(t.end(), off.begin(), off.end());
+    const int n_pass = (total + q.PF - 1) / q.PF;
+    const int per = (int)rup((size_t)(total + n_pass - 1) / n_pass, 256);   // passes of about equal rows
+    const int rbr = sizeof(T) == 2 ? kAttnRowsPrompt : kAttnRows;
+    struct Blk { int s, row, n, pos, rb, keys; };
+    std::vector<Blk> blk;
+    int s0 = 0;
+    for (int g0 = 0; g0 < total; g0 += per) {
+      PromptPass ps{};
+      ps.g0 = g0;
+      ps.rows = total - g0 < per ? total - g0 : per;
+      const int g1 = g0 + ps.rows;
+      while (off[s0 + 1] <= g0) ++s0;
+      ps.first_end = s0;
+      blk.clear();
+      t.resize(rup(t.size(), 4), 0);
+      ps.items = t.size();
+      for (int s = s0; s < ns && off[s] < g1; ++s) {
+        const int b = off[s] > g0 ? off[s] : g0, e = off[s + 1] < g1 ? off[s + 1] : g1;
+        const int pos = b - off[s], n = e - b, row = b - g0;
+        if (e == off[s + 1]) ps.n_end += 1;
+        for (int rb = 0; rb * rbr < n * q.G; ++rb) {
+          const int last = (n * q.G < (rb + 1) * rbr ? n * q.G : (rb + 1) * rbr) - 1;
+          blk.push_back(Blk{s, row, n, pos, rb, pos + last / q.G + 1});
+        }
+        for (int pg = pos / kPage; pg * kPage < pos + n; ++pg) {
+          const int lo = pg * kPage > pos ? pg * kPage : pos;
+          const int hi = (pg + 1) * kPage < pos + n ? (pg + 1) * kPage : pos + n;
+          const int32_t it[kPageItemInts] = {s, pg, row + lo - pos, (lo - pg * kPage) | (hi - lo) << 8};
+          t.insert(t.end(), it, it + kPageItemInts);
+          ps.n_items += 1;
+        }
+      }
+      // the longest key ranges first, so that the last blocks running are short ones
+      std::stable_sort(blk.begin(), blk.end(), [](const Blk& x, const Blk& y) { return x.keys > y.keys; });
+      ps.blocks = t.size();
+      ps.n_blocks = (int)blk.size();
+      for (const Blk& x : blk) {
+        const int32_t d[kAttnBlockInts] = {x.s, x.row, x.n, x.pos, x.rb, 0, 0, 0};
+        t.insert(t.end(), d, d + kAttnBlockInts);
+      }
+      out->passes.push_back(ps);
+    }
+  }
+
+  // The prompts' rows run in passes over all sequences together, so that every pass fills
+  // the chip and streams the weights once.
   int prefill(int ns, const int32_t* lens, const int32_t* ids, int budget, int32_t* first) override {
     const Plan& q = p;
     drop_graph();
     prefilled = false;
     ar_mode = false;
-    size_t off = 0;
-    int32_t* pf = at<int32_t>(q.pf_ints);
-    int32_t* tok = at<int32_t>(q.tokbuf);
-    for (int s = 0; s < ns; ++s) {
-      const int len = lens[s];
-      HIPCHK(hipMemcpyAsync(tok, ids + off, (size_t)len * 4, hipMemcpyHostToDevice, stream));
-      const int32_t* pt = at<int32_t>(q.page_table) + (size_t)s * q.pages_per_seq;
-      for (int c0 = 0; c0 < len; c0 += q.PF) {
-        const int n = len - c0 < q.PF ? len - c0 : q.PF;
-        set_ints(pf, 2, c0, n, 0, 0, stream);
-        embed_rows<T>(at<T>(q.embed), q.d, tok + c0, n, at<float>(q.x), q.d, stream);
-        for (int l = 0; l < q.L; ++l) {
-          const int slot = cond_slot(l);
-          LayerCtx c{n, q.PF, 1, 0, 1, 1, (n * q.G + kAttnRows - 1) / kAttnRows, kAttnRows, pf, pf + 1, pt,
-                     at<T>(q.kc) + (size_t)l * q.cache_layer_elems, at<T>(q.vc) + (size_t)l * q.cache_layer_elems,
-                     slot >= 0 ? at<T>(q.g) : nullptr, slot * q.d, &c0};
-          CHK(layer(tlayer(l), c));
-        }
-        CHK(context_append(n, q.PF, pf, nullptr, 0, pt));
-        if (c0 + n == len) {
-          rmsnorm<T, K>(at<float>(q.x) + (size_t)(n - 1) * q.d, q.d, at<T>(q.t_final_norm), q.d, cfg.rms_eps, 1,
-                        at<T>(q.xa), 16 * q.Kp_d, nullptr, 0, NormFold{}, stream);
-          const bool smp = sampling();
-          CHK(lm_head_argmax(1, at<uint64_t>(q.tkeys), smp ? at<float>(q.vlogits) : nullptr));
-          if (smp)
-            CHK(dists(at<float>(q.vlogits), 1, at<int32_t>(q.dist_ids_v), at<float>(q.dist_p_v), SAMPLE_FIRST, s,
-                      at<int32_t>(q.stok)));
-          first_token(at<int32_t>(q.state), s, at<uint64_t>(q.tkeys), smp ? at<int32_t>(q.stok) : nullptr, len, budget,
-                      at<int32_t>(q.first_tok), stream);
-        }
-        HIPCHK(hipGetLastError());
-      }
-      HIPCHK(hipStreamSynchronize(stream));   // the token buffer is reused by the next sequence
-      off += (size_t)len;
+    PromptTables pt;
+    prompt_tables(ns, lens, ids, &pt);
+    if (pt.tab.size() > q.pf_tab_ints) return fail(RT_ERR_CAPACITY, "prompt tables exceed their buffer");
+    HIPCHK(hipMemcpyAsync(ws + q.pf_tab, pt.tab.data(), pt.tab.size() * 4, hipMemcpyHostToDevice, stream));
+    const int32_t* tab = at<int32_t>(q.pf_tab);
+    const int32_t* off = tab + pt.off;
+    const int32_t* ptab = at<int32_t>(q.page_table);
+    const int rbr = sizeof(T) == 2 ? kAttnRowsPrompt : kAttnRows;
+    int rc = RT_OK;
+    for (const PromptPass& ps : pt.passes) {
+      if ((rc = prompt_pass(ps, tab, off, ptab, rbr, budget)) != RT_OK) break;
+    }
+    if (rc != RT_OK) {
+      (void)hipStreamSynchronize(stream);   // the tables are copied before they go
+      return rc;
     }
     fill_zero(ws + q.hd_keep, (size_t)q.R * q.d * q.ksz, stream);
     fill_zero(ws + q.ht_keep, (size_t)q.R * q.d * q.ksz, stream);
@@ -634,6 +690,39 @@ struct Engine : EngineBase {
     memcpy(first, h_out, (size_t)ns * 4);
     n_seqs = ns;
     prefilled = true;
+    return RT_OK;
+  }
+
+  int prompt_pass(const PromptPass& ps, const int32_t* tab, const int32_t* off, const int32_t* ptab, int rbr,
+                  int budget) {
+    const Plan& q = p;
+    const int n = ps.rows;
+    const int32_t* items = tab + ps.items;
+    embed_rows<T>(at<T>(q.embed), q.d, tab + ps.g0, n, at<float>(q.x), q.d, stream);
+    for (int l = 0; l < q.L; ++l) {
+      const int slot = cond_slot(l);
+      LayerCtx c{n, n, 1, 0, 1, 1, 1, rbr, nullptr, nullptr, ptab,
+                 at<T>(q.kc) + (size_t)l * q.cache_layer_elems, at<T>(q.vc) + (size_t)l * q.cache_layer_elems,
+                 slot >= 0 ? at<T>(q.g) : nullptr, slot * q.d, nullptr, l + 1 < q.L};
+      c.blocks = tab + ps.blocks; c.n_blocks = ps.n_blocks;
+      c.items = items; c.n_items = ps.n_items;
+      CHK(layer(tlayer(l), c));
+    }
+    CHK(context_append(n, n, nullptr, nullptr, 0, ptab, items, ps.n_items));
+    if (ps.n_end > 0) {   // first tokens of the sequences whose prompts end in this pass
+      float* last = at<float>(q.fcout);
+      gather_last(at<float>(q.x), q.d, off, ps.first_end, ps.n_end, ps.g0, last, stream);
+      rmsnorm<T, K>(last, q.d, at<T>(q.t_final_norm), q.d, cfg.rms_eps, ps.n_end, at<T>(q.xa), 16 * q.Kp_d, nullptr, 0,
+                    NormFold{}, stream);
+      const bool smp = sampling();
+      CHK(lm_head_argmax(ps.n_end, at<uint64_t>(q.tkeys), smp ? at<float>(q.vlogits) : nullptr));
+      if (smp)
+        CHK(dists(at<float>(q.vlogits), ps.n_end, at<int32_t>(q.dist_ids_v), at<float>(q.dist_p_v), SAMPLE_FIRST,
+                  ps.first_end, at<int32_t>(q.stok)));
+      first_tokens(at<int32_t>(q.state), ps.first_end, ps.n_end, at<uint64_t>(q.tkeys),
+                   smp ? at<int32_t>(q.stok) : nullptr, off, budget, at<int32_t>(q.first_tok), stream);
+    }
+    HIPCHK(hipGetLastError());
     return RT_OK;
   }
 

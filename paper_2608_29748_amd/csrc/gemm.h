@@ -80,6 +80,13 @@ struct QkvPostArgs {
   int n_part; size_t part_stride;   // n_part > 1: src holds k-slab partials, summed in slab order
 };
 
+// Prompt passes: rows of one page each.  items[i] = {sequence, page of the sequence,
+// activation row of its first token, first token within the page | token count << 8}; the
+// per-row fields rows_per_seq, seq_stride, pos0 and nrows of the arguments are unused.
+constexpr int kPageItemInts = 4;
+template <typename T>
+hipError_t qkv_post_pages(const QkvPostArgs& a, const int32_t* items, int n_items, hipStream_t s);
+
 // LM head with a fused argmax: logits = X * W^T over the vocabulary; each workgroup
 // reduces its columns to one (value, index) key per row in part_keys[wg][M]
 // (max value, lowest index among equal values), reduced by argmax_reduce.
@@ -106,8 +113,8 @@ enum GemmShape : int { SHAPE_SKINNY = 0, SHAPE_WIDE = 1 };
 // SHAPE_SKINNY: M <= 32 (and 33..64 with bf16 operands), 16, 32 or 64-row tiles, the k
 // range split across the workgroup's waves and reduced in LDS (no ksplit except k slabs
 // with EPI_PARTIAL).  SHAPE_WIDE: 128x128 tiles, optional ksplit.
-// SHAPE_WIDE with bf16 storage goes to the mid-size kernel (gemm_mid.hip) for 33..512
-// rows; otherwise (fp32 storage, more rows) 128x128 tiles.
+// SHAPE_WIDE with bf16 storage goes to the mid-size kernel (gemm_mid.hip) unless a k split
+// is asked for; otherwise (fp32 storage) 128x128 tiles.
 template <typename T>
 hipError_t gemm(const GemmArgs& a, int shape, bool a_f32, hipStream_t s);
 bool gemm_mid_supports(const GemmArgs& a);
@@ -117,7 +124,8 @@ hipError_t gemm_mid(const GemmArgs& a, bool a_f32, hipStream_t s);
 // with EPI_PARTIAL and this count
 int gemm_mid_store_slabs(const GemmArgs& a, bool a_f32);
 // k slabs (1..max_slabs) for a GEMM whose fp32 slab partials a later kernel adds: the
-// count that fills the chip in the fewest rounds of the cost model
+// count that fills the chip in the fewest rounds of the cost model (more than 512 rows: 1
+// where the direct epilogue is estimated faster than any slab count)
 int gemm_mid_partial_slabs(const GemmArgs& a, bool a_f32, int max_slabs);
 // Columns per workgroup of the mid-size kernel's argmax (LM head) launch over N columns
 // and M rows; it writes two partial keys per workgroup and row.

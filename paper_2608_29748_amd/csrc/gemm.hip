@@ -628,6 +628,97 @@ hipError_t qkv_post(const QkvPostArgs& a, hipStream_t s) {
 template hipError_t qkv_post<bf16_t>(const QkvPostArgs&, hipStream_t);
 template hipError_t qkv_post<float>(const QkvPostArgs&, hipStream_t);
 
+// One workgroup per (page of a sequence, head): the up to 16 rows of the pass that fall into
+// the page, sixteen lanes per row; lane c holds the pairs (l, l + hd/2), l = c*PL .. c*PL+PL-1.
+// The sum of squares is added in qkv_post_kernel's order: over the bits of l from the highest
+// down, which are the lane's four bits, then the element's.  V is transposed through LDS so
+// that a whole page is stored in 16-byte pieces (one wave per row and element-wise V stores
+// took 13.7 us for 512 rows of the Qwen3-4B shape).
+template <typename T, int HD>
+__global__ __launch_bounds__(256) void qkv_page_kernel(QkvPostArgs a, const int32_t* __restrict__ items) {
+  constexpr int half = HD / 2, PL = half / 16;
+  constexpr int VP = 16 + 16 / (int)sizeof(T);   // LDS pitch of an hd row of V
+  __shared__ __attribute__((aligned(16))) T sv[HD][VP];
+  const int32_t* it = items + (size_t)blockIdx.y * kPageItemInts;
+  const int s = it[0], pg = it[1], row0 = it[2], t0 = it[3] & 255, cnt = it[3] >> 8;
+  const int heads_per_layer = a.layer_cols / HD;
+  const int layer = blockIdx.x / heads_per_layer, hin = blockIdx.x % heads_per_layer;
+  const int qh = a.q_cols / HD, kvh = a.kv_cols / HD;
+  const int region = hin < qh ? 0 : (hin < qh + kvh ? 1 : 2);
+  const int head = region == 0 ? hin : (region == 1 ? hin - qh : hin - qh - kvh);
+  const int t = threadIdx.x >> 4, c = threadIdx.x & 15;
+  const bool valid = t >= t0 && t < t0 + cnt;
+  const int row = row0 + (valid ? t - t0 : 0), pos = pg * kPage + (valid ? t : t0);
+  const float* src = a.src + (size_t)row * a.lds + (size_t)layer * a.layer_cols + (size_t)hin * HD + c * PL;
+  float x0[PL], x1[PL];
+#pragma unroll
+  for (int e = 0; e < PL; ++e) { x0[e] = src[e]; x1[e] = src[half + e]; }
+  if (a.n_part > 1) {   // k-slab partials, added in slab order from zero
+#pragma unroll
+    for (int e = 0; e < PL; ++e) { x0[e] = 0.f + x0[e]; x1[e] = 0.f + x1[e]; }
+    for (int z = 1; z < a.n_part; ++z) {
+      const float* sz = src + (size_t)z * a.part_stride;
+#pragma unroll
+      for (int e = 0; e < PL; ++e) { x0[e] += sz[e]; x1[e] += sz[half + e]; }
+    }
+  }
+  if (region < 2) {
+    float q[PL];
+#pragma unroll
+    for (int e = 0; e < PL; ++e) q[e] = row16_sum(qk_sq(x0[e], x1[e]));
+    const float ss = PL == 4 ? (q[0] + q[2]) + (q[1] + q[PL - 1]) : q[0] + q[1];
+    const float inv = qk_inv(ss, HD, a.eps);
+    const T* nw = (const T*)(region == 0 ? a.q_norm : a.k_norm) + (size_t)layer * a.norm_layer_stride + c * PL;
+    const float* cs = a.rope + (size_t)pos * half + c * PL;
+    const float* sn = cs + (size_t)a.rope_max_pos * half;
+#pragma unroll
+    for (int e = 0; e < PL; ++e)
+      qk_norm_rope(x0[e], x1[e], inv, Elem<T>::to_f32(nw[e]), Elem<T>::to_f32(nw[half + e]), cs[e], sn[e]);
+    if (!valid) return;
+    T* dst;
+    if (region == 0) {
+      dst = (T*)a.q_out + (size_t)row * a.ldq + (size_t)head * HD + c * PL;
+    } else {
+      const int page = a.page_table[(size_t)s * a.max_pages + pg];
+      dst = (T*)a.kcache + (size_t)layer * a.cache_layer_stride +
+            ((size_t)page * a.n_kv_heads + head) * (size_t)kPage * HD + (size_t)t * HD + c * PL;
+    }
+#pragma unroll
+    for (int e = 0; e < PL; ++e) { dst[e] = Elem<T>::from_f32(x0[e]); dst[half + e] = Elem<T>::from_f32(x1[e]); }
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < PL; ++e) {
+    sv[c * PL + e][t] = Elem<T>::from_f32(x0[e]);
+    sv[half + c * PL + e][t] = Elem<T>::from_f32(x1[e]);
+  }
+  __syncthreads();
+  const int page = a.page_table[(size_t)s * a.max_pages + pg];
+  T* dst = (T*)a.vcache + (size_t)layer * a.cache_layer_stride +
+           ((size_t)page * a.n_kv_heads + head) * (size_t)kPage * HD;
+  constexpr int PE = 16 / (int)sizeof(T), PPR = 16 / PE;   // elements per piece, pieces per hd row
+  for (int p = threadIdx.x; p < HD * PPR; p += 256) {
+    const int h = p / PPR, k0 = p % PPR * PE;
+    if (k0 >= t0 && k0 + PE <= t0 + cnt) {
+      *reinterpret_cast<uint4*>(dst + (size_t)h * kPage + k0) = *reinterpret_cast<const uint4*>(&sv[h][k0]);
+    } else {   // the page's other tokens stay as they are
+      for (int e = 0; e < PE; ++e)
+        if (k0 + e >= t0 && k0 + e < t0 + cnt) dst[(size_t)h * kPage + k0 + e] = sv[h][k0 + e];
+    }
+  }
+}
+template <typename T>
+hipError_t qkv_post_pages(const QkvPostArgs& a, const int32_t* items, int n_items, hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  const dim3 grid((unsigned)((a.layer_cols / a.head_dim) * a.n_layers), (unsigned)n_items);
+  if (a.head_dim == 128) RT_LAUNCH((qkv_page_kernel<T, 128>), grid, dim3(256), 0, s, a, items);
+  else if (a.head_dim == 64) RT_LAUNCH((qkv_page_kernel<T, 64>), grid, dim3(256), 0, s, a, items);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+template hipError_t qkv_post_pages<bf16_t>(const QkvPostArgs&, const int32_t*, int, hipStream_t);
+template hipError_t qkv_post_pages<float>(const QkvPostArgs&, const int32_t*, int, hipStream_t);
+
 // ------------------------------------------------------------------ LM head + argmax
 
 constexpr int kLmTilesPerWave = 2;

@@ -1,5 +1,5 @@
-// Weight-streaming bf16 MFMA GEMM for 33..512 rows (batched verify / draft blocks and
-// prefill chunks): Y = X * W^T with the packed operands of gemm.h.
+// Weight-streaming bf16 MFMA GEMM for 33 or more rows (batched verify / draft blocks and
+// prompt passes): Y = X * W^T with the packed operands of gemm.h.
 //
 // A workgroup (4, 8 or 16 waves) owns MB rows x NB columns of the output and one k slab.  Per
 // 32-wide k tile it copies the MB/16 packed A fragments and NB/16 packed weight tiles
@@ -343,7 +343,7 @@ int gemm_mid_cols(int N, int M) {
 
 bool gemm_mid_supports(const GemmArgs& a) {
   const int k = a.e.kind;
-  if (a.e.M <= 32 || a.e.M > 512) return false;
+  if (a.e.M <= 32) return false;
   if (k == EPI_PARTIAL) return a.ksplit >= 1;
   return a.ksplit == 1;
 }
@@ -370,6 +370,10 @@ static void mid_launch(const GemmArgs& a, int MB, int NB, dim3 grid, hipStream_t
   // (8B shape) the same change measured no faster, and staging the tiles through
   // registers (16-byte loads two to four tiles ahead, written to LDS by the waves) instead
   // of direct-to-LDS copies was slower (gate|up 119 us).
+  // 256 x 256 with several row tiles (prompt passes, LM heads of more than 256 rows): 8
+  // waves with the fragment double buffer, 64 x 128 a wave (12 KiB of LDS reads per 32
+  // MFMAs against 10 per 16 with 16 waves): 4096 x 24576 x 4096 697 -> 650 us, 4096 x 19456
+  // x 2560 381 -> 364 us; with one row tile (14B LM head) the 16 waves stay, 3% faster there.
   // The output tile is split spatially, so every element is accumulated over k in the
   // same order either way.
   if (MB == 128) {
@@ -392,12 +396,20 @@ static void mid_launch(const GemmArgs& a, int MB, int NB, dim3 grid, hipStream_t
       else if (NB == 160) RT_LAUNCH((gemm_mid_kernel<256, 160, 5, false, 16, true>), grid, dim3(1024), 0, s, a);
       else if (NB == 192 && one) RT_LAUNCH((gemm_mid_kernel<256, 192, 5, false, 16, true, true>), grid, dim3(1024), 0, s, a);
       else if (NB == 192) RT_LAUNCH((gemm_mid_kernel<256, 192, 5, false, 16, true>), grid, dim3(1024), 0, s, a);
-      else RT_LAUNCH((gemm_mid_kernel<256, 256, 3, false, 16>), grid, dim3(1024), 0, s, a);
+      else if (one) RT_LAUNCH((gemm_mid_kernel<256, 256, 3, false, 16>), grid, dim3(1024), 0, s, a);
+      else RT_LAUNCH((gemm_mid_kernel<256, 256, 4, false, 8, true>), grid, dim3(512), 0, s, a);
     }
   }
 }
 
-// Tile width and k slabs.  A workgroup streams (MB + NB) / 16 KiB through LDS per k
+// More than 512 rows (prompt passes): microseconds per 32-wide k tile of one round of 256
+// workgroups, measured with the chip full (K = 2560..17408, 1024..4096 rows; e.g. 4096 x
+// 19456 x 2560: 256 columns 364 us, 160 400, 128 407; 4096 x 2560 x 9728: 160 columns
+// (256 workgroups) 172 us, 256 213, 128 263).  The rounds decide: the widest tile moves
+// the fewest LDS bytes per MFMA, a narrower one may fill the last round.
+static double big_step_us(int NB) { return NB == 64 ? 0.40 : NB == 128 ? 0.52 : NB == 160 ? 0.60 : 0.85; }
+
+// Tile width and k slabs, up to 512 rows.  A workgroup streams (MB + NB) / 16 KiB through LDS per k
 // tile, about one workgroup per compute unit is resident for the wide tiles, and the
 // grid runs in rounds of 256 workgroups, so the estimated time of a choice is
 // rounds x (MB + NB) / 16 x k tiles per slab (slabs cost an extra pass over the
@@ -410,9 +422,11 @@ static MidPlan mid_plan(const GemmArgs& a, int MB, bool a_f32) {
   const size_t slab = (size_t)M * N;
   MidPlan best{64, 1};
   double best_cost = 1e30;
-  for (int NB : {64, 96, 128, 160, 192}) {
+  const bool big = M > 512;
+  for (int NB : {64, 96, 128, 160, 192, 256}) {
     if ((NB >= 160 || NB == 96) && a_f32) continue;
-    if (NB == 160 && (MB != 256 || a.e.kind == EPI_PARTIAL)) continue;
+    if ((NB == 256 && !big) || (NB == 192 && big)) continue;
+    if ((NB == 160 || NB == 256) && (MB != 256 || a.e.kind == EPI_PARTIAL)) continue;
     if (NB == 96 && (MB != 128 || a.e.kind == EPI_PARTIAL)) continue;
     const long tiles = (long)((N + NB - 1) / NB) * ((M + MB - 1) / MB);
     int ks = 1;
@@ -427,7 +441,7 @@ static MidPlan mid_plan(const GemmArgs& a, int MB, bool a_f32) {
     }
     if ((NB >= 160 || NB == 96) && ks > 1) continue;   // tiles for large outputs only
     const double rounds = (double)((tiles * ks + 255) / 256);
-    double cost = rounds * (ai + NB / 16) * ((KT + ks - 1) / ks);
+    double cost = rounds * (big ? big_step_us(NB) : (double)(ai + NB / 16)) * ((KT + ks - 1) / ks);
     // slabs are written and read back once (mostly from cache): a quarter of their
     // bytes relative to the weights'
     if (ks > 1 && a.e.kind != EPI_PARTIAL) cost *= 1.0 + (double)ks * M / (KT * kTileK);
@@ -439,13 +453,27 @@ static MidPlan mid_plan(const GemmArgs& a, int MB, bool a_f32) {
 int gemm_mid_store_slabs(const GemmArgs& a, bool a_f32) {
   GemmArgs g = a;
   if (g.e.kind == EPI_PARTIAL) g.e.kind = EPI_STORE_F32;
-  if (g.e.M <= 32 || g.e.M > 512) return 1;
+  if (g.e.M <= 32) return 1;
   return mid_plan(g, g.e.M <= 128 ? 128 : 256, a_f32).ks;
 }
 
+// Fastest column tile of a GEMM of more than 512 rows with ks slabs (1: any tile).
+static int mid_tile_big(const GemmArgs& a, int ks, bool a_f32) {
+  int best = 64;
+  double best_cost = 1e30;
+  for (int NB : {64, 128, 160, 256}) {
+    if (NB > 128 && (a_f32 || ks > 1)) continue;
+    const long tiles = (long)((a.e.N + NB - 1) / NB) * ((a.e.M + 255) / 256);
+    const double cost = (double)((tiles * ks + 255) / 256) * big_step_us(NB);
+    if (cost < best_cost) { best_cost = cost; best = NB; }
+  }
+  return best;
+}
+
 int gemm_mid_partial_slabs(const GemmArgs& a, bool a_f32, int max_slabs) {
-  if (a.e.M <= 32 || a.e.M > 512) return 1;
+  if (a.e.M <= 32) return 1;
   const int MB = a.e.M <= 128 ? 128 : 256;
+  const bool big = a.e.M > 512;
   GemmArgs g = a;
   g.e.kind = EPI_PARTIAL;
   int best = 1;
@@ -453,11 +481,23 @@ int gemm_mid_partial_slabs(const GemmArgs& a, bool a_f32, int max_slabs) {
   for (int ks = 1; ks <= max_slabs; ++ks) {
     if ((size_t)ks * g.e.M * g.e.N > a.partial_floats) break;
     g.ksplit = ks;
-    const MidPlan pl = mid_plan(g, MB, a_f32);
     const int KT = a.Kp / kTileK;
+    double cost;
+    if (big) {
+      // one slab: the direct epilogue's best tile; more: slabs written once and read once
+      // by the norm that adds them, at about 4 bytes per picosecond
+      g.e.kind = ks == 1 ? EPI_RESID : EPI_PARTIAL;
+      if (ks > KT / 8 && ks > 1) break;
+      const int NB = mid_tile_big(g, ks, a_f32);
+      const long tiles = (long)((g.e.N + NB - 1) / NB) * ((g.e.M + MB - 1) / MB);
+      cost = (double)((tiles * ks + 255) / 256) * big_step_us(NB) * ((KT + ks - 1) / ks) +
+             (ks > 1 ? 8.0e-6 * ks * g.e.M * g.e.N / 4.0 : 0.0);
+      if (cost < best_cost) { best_cost = cost; best = ks; }
+      continue;
+    }
+    const MidPlan pl = mid_plan(g, MB, a_f32);
     const long tiles = (long)((g.e.N + pl.NB - 1) / pl.NB) * ((g.e.M + MB - 1) / MB);
-    const double cost = (double)((tiles * ks + 255) / 256) * ((MB / 16) * (a_f32 ? 2 : 1) + pl.NB / 16) *
-                        ((KT + ks - 1) / ks);
+    cost = (double)((tiles * ks + 255) / 256) * ((MB / 16) * (a_f32 ? 2 : 1) + pl.NB / 16) * ((KT + ks - 1) / ks);
     if (cost < best_cost) { best_cost = cost; best = ks; }
   }
   return best;

@@ -20,7 +20,12 @@ size_t weight_elems(const rt_config* c, int i);
 
 inline size_t rup(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-constexpr int kPrefillChunk = 512;     // prompt rows per prefill pass
+// Prompt rows per prefill pass: the prompts of a call are laid end to end and run in passes
+// of at most this many rows (fewer where max_batch * max_seq_len is smaller).  At 4096 rows
+// the Qwen3-4B layer GEMMs fill the chip at 1.05-1.27 PFLOP/s, against 0.42-0.94 at 512
+// (o: 32 workgroups of 256 x 160); the activations of a pass take about 120 KB a row there.
+constexpr int kPrefillRows = 4096;
+constexpr int kPrefillRowsMin = 512;
 constexpr int kMaxTiles = 1 << 16;     // split-K arrival counters
 constexpr size_t kPartialFloats = (size_t)8 << 20;   // split-K partial capacity (32 MiB)
 constexpr int kResidSplits = 4;   // k slabs of the round's o / down projections (skinny kernel)
@@ -43,7 +48,6 @@ struct Plan {
   int attn_rb, attn_splits;              // round attention row blocks / key splits
   int attn_rows;                         // round attention rows per block (64, or 96)
   int ar_rb, ar_splits;                  // target-only steps: 64-row attention blocks / key splits
-  int pf_rb;
   size_t cache_layer_elems;
   // byte offsets into the workspace
   size_t embed, lm_head, t_final_norm, d_final_norm, fc, hidden_norm, ctxkv, ctx_knorm, wc, wg, wv;
@@ -52,9 +56,12 @@ struct Plan {
   size_t kc, vc, dkc, dvc;
   size_t page_table, rope, state, pf_ints, first_tok, counters, partial, opart, mlpart, attn_plan;
   size_t x, xa, qbuf, attn, mlp, g, fcout, fa, etilde, mu, er, gate;
-  size_t hd_keep, ht_keep, dlogits, vlogits, dkeys, tkeys, dtok, ttok, out_tok, out_n, out_a, tokbuf;
+  size_t hd_keep, ht_keep, dlogits, vlogits, dkeys, tkeys, dtok, ttok, out_tok, out_n, out_a;
+  size_t pf_tab, pf_tab_ints;    // prompt tables of a prefill (tokens, offsets, attention blocks, page items)
   size_t qkvf, part_keys;        // fp32 q|k|v projection output; LM-head partial argmax keys
-  size_t rpart;                  // k-slab partials of the deferred residual GEMMs [kResidSplitsMax][rpart_rows][d]
+  size_t rpart;                  // k-slab partials of the deferred residual GEMMs: [kResidSplitsMax][rpart_rows][d]
+                                 // in rounds, [slabs][rows of the pass][d] in prompt passes
+  size_t rpart_floats;           // its capacity
   size_t ar_tok;                 // target-only step tokens [bmax][kArMaxSteps]
   size_t dist_ids_d, dist_p_d;   // sampling: drafter filtered distributions [R][RT_MAX_TOP_K]
   size_t dist_ids_v, dist_p_v;   // sampling: target filtered distributions [R][RT_MAX_TOP_K]

@@ -71,9 +71,14 @@ void accept(int32_t* state, const int32_t* dtok, const uint64_t* tkeys, int32_t*
 void ar_commit(int32_t* state, const uint64_t* tkeys, const int32_t* sampled, int n_seqs, int32_t* out, int ld_out,
                int32_t* step, hipStream_t s);
 void set_ints(int32_t* dst, int n, int v0, int v1, int v2, int v3, hipStream_t s);
-// sampled (may be null): drawn first tokens per sequence instead of the argmax key.
-void first_token(int32_t* state, int seq, const uint64_t* keys, const int32_t* sampled, int prompt_len, int budget,
-                 int32_t* first_out, hipStream_t s);
+// Round state and first tokens of sequences seq0 .. seq0+n-1 after their prompts (lengths
+// off[s+1] - off[s]): the argmax keys[i] of sequence seq0+i, or, with sampled (may be null),
+// the drawn token sampled[seq0+i].
+void first_tokens(int32_t* state, int seq0, int n, const uint64_t* keys, const int32_t* sampled, const int32_t* off,
+                  int budget, int32_t* first_out, hipStream_t s);
+// out[i] = row off[seq0+i+1] - 1 - g0 of x: the last prompt rows of n consecutive sequences
+// within a pass that starts at token g0 of the concatenated prompts.
+void gather_last(const float* x, int d, const int32_t* off, int seq0, int n, int g0, float* out, hipStream_t s);
 void fill_zero(void* p, size_t bytes, hipStream_t s);
 // Plain read of bytes (a multiple of 16) at p by `grid` workgroups of 256 threads.
 void stream_read(const void* p, size_t bytes, int grid, uint32_t* sink, hipStream_t s);

@@ -384,11 +384,12 @@ void set_ints(int32_t* dst, int n, int v0, int v1, int v2, int v3, hipStream_t s
   RT_LAUNCH(set_ints_kernel, dim3(1), dim3(64), 0, s, dst, n, v0, v1, v2, v3);
 }
 
-__global__ void first_token_kernel(int32_t* st_all, int sq, const uint64_t* keys, const int32_t* sampled, int plen,
-                                   int budget, int32_t* first_out) {
+__global__ void first_tokens_kernel(int32_t* st_all, int seq0, const uint64_t* keys, const int32_t* sampled,
+                                    const int32_t* off, int budget, int32_t* first_out) {
   if (threadIdx.x != 0) return;
+  const int sq = seq0 + blockIdx.x, plen = off[sq + 1] - off[sq];
   int32_t* st = st_all + sq * kStateFields;
-  const int tok = sampled ? sampled[sq] : key_index(keys[0]);
+  const int tok = sampled ? sampled[sq] : key_index(keys[blockIdx.x]);
   st[ST_SEQ_LEN] = plen;
   st[ST_ANCHOR] = tok;
   st[ST_R] = 0;
@@ -400,10 +401,20 @@ __global__ void first_token_kernel(int32_t* st_all, int sq, const uint64_t* keys
   st[ST_ROUND] = 0;
   first_out[sq] = tok;
 }
-void first_token(int32_t* state, int seq, const uint64_t* keys, const int32_t* sampled, int prompt_len, int budget,
-                 int32_t* first_out, hipStream_t s) {
-  RT_LAUNCH(first_token_kernel, dim3(1), dim3(64), 0, s, state, seq, keys, sampled, prompt_len, budget,
-                     first_out);
+void first_tokens(int32_t* state, int seq0, int n, const uint64_t* keys, const int32_t* sampled, const int32_t* off,
+                  int budget, int32_t* first_out, hipStream_t s) {
+  if (n <= 0) return;
+  RT_LAUNCH(first_tokens_kernel, dim3(n), dim3(64), 0, s, state, seq0, keys, sampled, off, budget, first_out);
+}
+
+__global__ void gather_last_kernel(const float* __restrict__ x, int d, const int32_t* __restrict__ off, int seq0,
+                                   int g0, float* __restrict__ out) {
+  const float* src = x + (size_t)(off[seq0 + blockIdx.x + 1] - 1 - g0) * d;
+  for (int i = threadIdx.x; i < d; i += blockDim.x) out[(size_t)blockIdx.x * d + i] = src[i];
+}
+void gather_last(const float* x, int d, const int32_t* off, int seq0, int n, int g0, float* out, hipStream_t s) {
+  if (n <= 0) return;
+  RT_LAUNCH(gather_last_kernel, dim3(n), dim3(256), 0, s, x, d, off, seq0, g0, out);
 }
 
 __global__ void fill_zero_kernel(uint4* p, size_t n16) {

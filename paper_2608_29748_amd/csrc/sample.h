@@ -14,7 +14,7 @@ enum DrawPurpose : int { U_DRAFT = 1, U_ACCEPT = 2, U_RESAMPLE = 3, U_FIRST = 4,
 enum SampleMode : int {
   SAMPLE_NONE = 0,    // distributions only (verify rows)
   SAMPLE_DRAFT = 1,   // rows (s, i) of draft blocks: draw block positions i >= 1 into tok_out[row]
-  SAMPLE_FIRST = 2,   // one row of sequence `seq0`: the prefill's first token into tok_out[seq0]
+  SAMPLE_FIRST = 2,   // row i = sequence seq0 + i: the prefill's first tokens into tok_out[seq0 + i]
   SAMPLE_STEP = 3,    // row s = sequence s: a target-only step into tok_out[s]
 };
 

@@ -136,7 +136,7 @@ __global__ __launch_bounds__(64) void filtered_dist_kernel(DistArgs a, const uin
     purpose = U_DRAFT;
     if (pos == 0) return;                   // the anchor row proposes nothing
   } else if (a.mode == SAMPLE_FIRST) {
-    s = a.seq0;
+    s = a.seq0 + row;
     purpose = U_FIRST;
   } else {
     s = row;

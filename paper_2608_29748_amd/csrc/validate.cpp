@@ -115,7 +115,10 @@ int make_plan(const rt_config* c, Plan* p) {
   q.pages_per_seq = (q.T + 15) / 16;
   q.n_pages = q.bmax * q.pages_per_seq;
   q.R = q.bmax * q.bk;
-  q.PF = kPrefillChunk;
+  {
+    const size_t all = rup((size_t)q.bmax * q.T, 256);
+    q.PF = all > kPrefillRows ? kPrefillRows : all < kPrefillRowsMin ? kPrefillRowsMin : (int)all;
+  }
   q.Mrows = (int)rup((size_t)(q.R > q.PF ? q.R : q.PF), 128);
   // one row block per sequence and KV head when the block has at most 96 (token, head)
   // rows (bf16), so each KV head's keys are read once
@@ -135,7 +138,6 @@ int make_plan(const rt_config* c, Plan* p) {
   q.attn_splits = key_splits(q.attn_rb);
   q.ar_rb = (q.G + kAttnRowsAr - 1) / kAttnRowsAr;   // one query token: G rows per KV head
   q.ar_splits = key_splits(q.ar_rb);
-  q.pf_rb = (q.PF * q.G + 63) / 64;
   q.cache_layer_elems = (size_t)q.n_pages * q.Hkv * 16 * q.hd;
 
   size_t off = 0;
@@ -187,10 +189,11 @@ int make_plan(const rt_config* c, Plan* p) {
   q.counters = take((size_t)kMaxTiles * 4);
   q.partial = take(kPartialFloats * 4);
   q.rpart_rows = q.R > 32 ? q.R : 32;
-  q.rpart = take((size_t)kResidSplitsMax * q.rpart_rows * q.d * 4);
+  // prompt passes: two slabs of a full pass, or more slabs of fewer rows
+  q.rpart_floats = (size_t)kResidSplitsMax * q.rpart_rows * q.d;
+  if (q.rpart_floats < (size_t)2 * q.PF * q.d) q.rpart_floats = (size_t)2 * q.PF * q.d;
+  q.rpart = take(q.rpart_floats * 4);
   {
-    size_t rb = q.attn_rb > q.pf_rb ? q.attn_rb : q.pf_rb;
-    (void)rb;
     // per KV head one partial block per slot, plus one per unit boundary (a slot of the
     // spanning plan writes one block per unit it meets)
     size_t rows = (size_t)q.Hkv * ((size_t)q.bmax * q.attn_rb * (q.attn_splits + 1) - 1) * q.attn_rows;
@@ -227,14 +230,20 @@ int make_plan(const rt_config* c, Plan* p) {
     q.lm_parts = (q.V + 31) / 32 / 8 + 1;                 // skinny LM head workgroups
     if (2 * ((q.V + 63) / 64) > q.lm_parts) q.lm_parts = 2 * ((q.V + 63) / 64);   // mid-size: 2 per workgroup
     if (q.lm_parts < kLmPartsMin) q.lm_parts = kLmPartsMin;   // LDS-staged skinny LM head
-    q.part_keys = take((size_t)q.lm_parts * M * 8);
+    q.part_keys = take((size_t)q.lm_parts * rup(q.R, 32) * 8);   // the LM head runs on at most R rows
   }
   q.dtok = take((size_t)q.R * 4);
   q.ttok = take((size_t)q.R * 4);
   q.out_tok = take((size_t)q.R * 4);
   q.out_n = take((size_t)q.bmax * 4);
   q.out_a = take((size_t)q.bmax * 4);
-  q.tokbuf = take((size_t)q.T * 4);
+  {
+    // tokens and offsets; per (sequence, pass) segment at most rows / 64 + 1 attention blocks
+    // and rows / 16 + 2 page items
+    const size_t tok = (size_t)q.bmax * q.T, seg = (size_t)q.bmax + tok / q.PF + 2;
+    q.pf_tab_ints = tok + q.bmax + 1 + 8 * (tok * q.G / 64 + seg) + 4 * (tok / 16 + 2 * seg) + 64;
+    q.pf_tab = take(q.pf_tab_ints * 4);
+  }
   q.ar_tok = take((size_t)q.bmax * kArMaxSteps * 4);
   q.dist_ids_d = take((size_t)q.R * RT_MAX_TOP_K * 4);
   q.dist_p_d = take((size_t)q.R * RT_MAX_TOP_K * 4);
