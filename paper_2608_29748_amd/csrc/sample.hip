@@ -78,24 +78,70 @@ __device__ __forceinline__ uint64_t wave_merge_top(uint64_t list, uint64_t batch
   return m;
 }
 
-// Stage 1: workgroup (c, row) keeps the 64 largest keys of logits c*kChunk .. of its row:
-// each wave folds batches of 64 logits into a running top-64, then wave 0 folds the
-// other waves' lists and stores its top_k keys.
+// Stage 1: workgroup (c, row) keeps the top_k largest keys of logits c*kChunk .. of its row.
+// A lower bound of the top_k-th key comes first: every wave sorts its 64 lanes' maxima, of
+// which the top_k-th is reached by at least top_k logits, and the largest of the four waves'
+// bounds holds for the chunk.  The few logits that reach it (about 25 of 8192 random ones)
+// are collected in LDS and sorted by wave 0.  Where more than kCandMax logits tie or reach
+// the bound, every wave folds all its logits into a running top-64 instead (64 at a time).
+// 128 rows of 151936 (78 MB of logits): 217 us with every 64 logits sorted, 39 us now; one
+// row 59 us and 12 us.
+constexpr int kCandMax = 512;
 __global__ __launch_bounds__(kDistThreads) void topk_chunk_kernel(DistArgs a, uint64_t* cand, int n_chunks) {
-  __shared__ uint64_t lists[kDistThreads / 64][64];
+  constexpr int NW = kDistThreads / 64, NV = kChunk / kDistThreads;   // values per thread
+  __shared__ uint64_t lists[NW][64];
+  __shared__ uint64_t found[kCandMax];
+  __shared__ uint64_t bound[NW];
+  __shared__ int n_found;
   const int c = blockIdx.x, row = blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const float* z = a.logits + (size_t)row * a.ldl;
   const int i0 = c * kChunk, i1 = min(a.V, i0 + kChunk);
-  uint64_t top = 0ull;
-  for (int b = i0 + w * 64; b < i1; b += kDistThreads) {
-    const int i = b + lane;
-    const uint64_t k = i < i1 ? logit_key(z[i], i) : 0ull;
-    top = wave_merge_top(top, wave_sort_desc(k, lane), lane);
+  if (threadIdx.x == 0) n_found = 0;
+  float v[NV];
+  uint64_t best = 0ull;   // 0: padding, below every logit's key
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = i0 + j * kDistThreads + threadIdx.x;
+    v[j] = i < i1 ? z[i] : 0.f;
   }
-  lists[w][lane] = top;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = i0 + j * kDistThreads + threadIdx.x;
+    if (i < i1) best = kmax(best, logit_key(v[j], i));
+  }
+  const uint64_t s = wave_sort_desc(best, lane);
+  if (lane == a.top_k - 1) bound[w] = s;
   __syncthreads();
-  if (w != 0) return;
-  for (int v = 1; v < kDistThreads / 64; ++v) top = wave_merge_top(top, lists[v][lane], lane);
+  uint64_t thr = bound[0];
+#pragma unroll
+  for (int u = 1; u < NW; ++u) thr = kmax(thr, bound[u]);
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = i0 + j * kDistThreads + threadIdx.x;
+    const uint64_t k = logit_key(v[j], i);
+    if (i < i1 && k >= thr) {
+      const int at = atomicAdd(&n_found, 1);
+      if (at < kCandMax) found[at] = k;
+    }
+  }
+  __syncthreads();
+  const int nf = n_found;
+  uint64_t top = 0ull;
+  if (nf <= kCandMax) {
+    if (w != 0) return;
+    for (int b = 0; b < nf; b += 64)
+      top = wave_merge_top(top, wave_sort_desc(b + lane < nf ? found[b + lane] : 0ull, lane), lane);
+  } else {
+    for (int b = i0 + w * 64; b < i1; b += kDistThreads) {
+      const int i = b + lane;
+      const uint64_t k = i < i1 ? logit_key(z[i], i) : 0ull;
+      top = wave_merge_top(top, wave_sort_desc(k, lane), lane);
+    }
+    lists[w][lane] = top;
+    __syncthreads();
+    if (w != 0) return;
+    for (int u = 1; u < NW; ++u) top = wave_merge_top(top, lists[u][lane], lane);
+  }
   if (lane < a.top_k) cand[((size_t)row * n_chunks + c) * kMaxTopK + lane] = top;
 }
 
