@@ -236,9 +236,12 @@ struct Engine : EngineBase {
     if (k_logical <= 0) k_logical = Kp;
     e.M = M;
     e.N = N;
-    // skinny up to 32 rows, and up to 64 rows with bf16 operands; the test hook (flags & 4)
-    // keeps 33..64 rows on the wide split-k path
-    const bool skinny = M <= 32 || (M <= 64 && sizeof(T) == 2 && !af32 && !(flags & 4));
+    // skinny up to 32 rows; 33..64 rows of bf16 operands where the mid-size kernel's tiles
+    // would leave more than half the chip idle (fewer than 128 of 96 columns: the 4B q|k|v,
+    // 6144 columns, 13.9 us against 14.7) and no slabs are asked for; the test hook (flags &
+    // 4) keeps 33..64 rows on the wide split-k path
+    const bool skinny = M <= 32 || (M <= 64 && sizeof(T) == 2 && !af32 && e.kind != EPI_PARTIAL && N < 128 * 96 &&
+                                    !(flags & 4));
     const int shape = skinny ? SHAPE_SKINNY : SHAPE_WIDE;
     const int KT = Kp / 32;
     int ks = 1;
@@ -284,6 +287,8 @@ struct Engine : EngineBase {
     return gemm_mid_store_slabs(g, false);
   }
 
+  // Rounds of at least this many rows post-process q|k|v by page (qkv_post_pages)
+  static constexpr int kPageRows = 96;
   struct LayerCtx {
     int M, rows_per_seq, n_seqs, stride, causal, splits, rb, rb_rows;
     const int32_t* pos0;
@@ -320,7 +325,7 @@ struct Engine : EngineBase {
                  bool capture) {
     const Plan& q = p;
     EpiArgs e{};
-    // skinny rows: 4 slabs; 65 rows or more (mid-size kernel): the slab count that fills
+    // up to 32 rows (skinny kernels): 4 slabs; more (mid-size kernel): the slab count that fills
     // the chip (e.g. 40 column tiles x 6 slabs at the 14B shape), at most 8; one slab (large
     // prompt passes) adds to x in the epilogue instead.  Slabs are rpart_rows apart in
     // rounds; prompt passes pack them.
@@ -329,7 +334,7 @@ struct Engine : EngineBase {
     int ks = 1;
     if (defer) {
       ks = kResidSplits;
-      if (c.M > 64 && sizeof(T) == 2) {
+      if (c.M > 32 && sizeof(T) == 2) {
         GemmArgs g{};
         g.Kp = Kp; g.partial_floats = c.blocks ? q.rpart_floats : (size_t)kResidSplitsMax * stride;
         g.e.kind = EPI_PARTIAL; g.e.M = c.M; g.e.N = q.d;
@@ -383,7 +388,8 @@ struct Engine : EngineBase {
       qp.rope = at<float>(q.rope); qp.rope_max_pos = q.T; qp.eps = cfg.rms_eps;
       qp.rows_per_seq = c.rows_per_seq; qp.seq_stride = c.stride; qp.pos0 = c.pos0; qp.nrows = nullptr;
       prof_begin(RT_K_QKV_POST, (double)c.M * q.qkvN * (4 * qks + sizeof(T)), 0);
-      HIPCHK(c.items ? qkv_post_pages<T>(qp, c.items, c.n_items, stream) : qkv_post<T>(qp, stream));
+      HIPCHK(c.items ? qkv_post_pages<T>(qp, c.items, c.n_items, stream)
+             : c.M >= kPageRows ? qkv_post_pages<T>(qp, nullptr, c.n_seqs, stream) : qkv_post<T>(qp, stream));
       prof_end();
       CHK(trace_item(c.trace, TI_Q, at<T>(q.qbuf)));
     }
@@ -520,7 +526,8 @@ struct Engine : EngineBase {
     qp.rope = at<float>(q.rope); qp.rope_max_pos = q.T; qp.eps = cfg.rms_eps;
     qp.rows_per_seq = rows_per_seq; qp.seq_stride = stride; qp.pos0 = pos0; qp.nrows = nrows;
     prof_begin(RT_K_QKV_POST, (double)M * q.LD * 2 * q.kvN * (4 + sizeof(T)), 0);
-    HIPCHK(items ? qkv_post_pages<T>(qp, items, n_items, stream) : qkv_post<T>(qp, stream));
+    HIPCHK(items ? qkv_post_pages<T>(qp, items, n_items, stream)
+           : M >= kPageRows ? qkv_post_pages<T>(qp, nullptr, M / rows_per_seq, stream) : qkv_post<T>(qp, stream));
     prof_end();
     return RT_OK;
   }

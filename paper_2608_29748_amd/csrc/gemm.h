@@ -80,9 +80,10 @@ struct QkvPostArgs {
   int n_part; size_t part_stride;   // n_part > 1: src holds k-slab partials, summed in slab order
 };
 
-// Prompt passes: rows of one page each.  items[i] = {sequence, page of the sequence,
-// activation row of its first token, first token within the page | token count << 8}; the
-// per-row fields rows_per_seq, seq_stride, pos0 and nrows of the arguments are unused.
+// The same by KV page.  Prompt passes: items[i] = {sequence, page of the sequence, activation
+// row of its first token, first token within the page | token count << 8}; rows_per_seq,
+// seq_stride, pos0 and nrows of the arguments are unused.  Rounds (items null): n_items is
+// the number of sequences.
 constexpr int kPageItemInts = 4;
 template <typename T>
 hipError_t qkv_post_pages(const QkvPostArgs& a, const int32_t* items, int n_items, hipStream_t s);
@@ -110,7 +111,7 @@ template <typename T>
 void pack_interleaved(const T* Wa, const T* Wb, int N, int K, int Kp, T* out, hipStream_t s);
 
 enum GemmShape : int { SHAPE_SKINNY = 0, SHAPE_WIDE = 1 };
-// SHAPE_SKINNY: M <= 32 (and 33..64 with bf16 operands), 16, 32 or 64-row tiles, the k
+// SHAPE_SKINNY: M <= 32 (and 33..64 with bf16 operands and no slabs), 16, 32 or 64-row tiles, the k
 // range split across the workgroup's waves and reduced in LDS (no ksplit except k slabs
 // with EPI_PARTIAL).  SHAPE_WIDE: 128x128 tiles, optional ksplit.
 // SHAPE_WIDE with bf16 storage goes to the mid-size kernel (gemm_mid.hip) unless a k split

@@ -497,13 +497,12 @@ hipError_t gemm(const GemmArgs& a, int shape, bool a_f32, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (shape == SHAPE_SKINNY) {
     if (M > 32) {
-      // 33..64 rows (bf16 operands): 64-row tiles, eight waves over k, two k tiles in
-      // flight per wave; 32 columns, or 64 per k slab of a split reduction
+      // 33..64 rows (bf16 operands): 64-row tiles of 32 columns, eight waves over k, two k
+      // tiles in flight per wave
       if constexpr (sizeof(T) != 2) return hipErrorInvalidValue;
       if (M > 64 || a_f32) return hipErrorInvalidValue;
-      if ((a.e.kind == EPI_PARTIAL) != (a.ksplit > 1) || a.ksplit < 1) return hipErrorInvalidValue;
-      if (a.ksplit > 1) RT_LAUNCH((gemm16_kernel<T, false, 4, 4, 8, 2>), dim3((N + 63) / 64, 1, a.ksplit), dim3(512), 0, s, a);
-      else RT_LAUNCH((gemm16_kernel<T, false, 4, 2, 8, 2>), dim3((N + 31) / 32, 1, 1), dim3(512), 0, s, a);
+      if (a.e.kind == EPI_PARTIAL || a.ksplit != 1) return hipErrorInvalidValue;
+      RT_LAUNCH((gemm16_kernel<T, false, 4, 2, 8, 2>), dim3((N + 31) / 32, 1, 1), dim3(512), 0, s, a);
       return hipGetLastError();
     }
     // tile width, waves and loads in flight per shape class (measured on the Qwen3 layer
@@ -628,19 +627,34 @@ hipError_t qkv_post(const QkvPostArgs& a, hipStream_t s) {
 template hipError_t qkv_post<bf16_t>(const QkvPostArgs&, hipStream_t);
 template hipError_t qkv_post<float>(const QkvPostArgs&, hipStream_t);
 
-// One workgroup per (page of a sequence, head): the up to 16 rows of the pass that fall into
-// the page, sixteen lanes per row; lane c holds the pairs (l, l + hd/2), l = c*PL .. c*PL+PL-1.
+// One workgroup per (page of a sequence, head): the up to 16 rows that fall into the page,
+// from the item list of a prompt pass or, in rounds (items null), row block i of grid y =
+// page i % np of sequence i / np past the page of its first position;
+// sixteen lanes per row; lane c holds the pairs (l, l + hd/2), l = c*PL .. c*PL+PL-1.
 // The sum of squares is added in qkv_post_kernel's order: over the bits of l from the highest
 // down, which are the lane's four bits, then the element's.  V is transposed through LDS so
 // that a whole page is stored in 16-byte pieces (one wave per row and element-wise V stores
 // took 13.7 us for 512 rows of the Qwen3-4B shape).
+__host__ __device__ __forceinline__ int round_pages(int rows_per_seq) { return (rows_per_seq + kPage - 1) / kPage + 1; }
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void qkv_page_kernel(QkvPostArgs a, const int32_t* __restrict__ items) {
   constexpr int half = HD / 2, PL = half / 16;
   constexpr int VP = 16 + 16 / (int)sizeof(T);   // LDS pitch of an hd row of V
   __shared__ __attribute__((aligned(16))) T sv[HD][VP];
-  const int32_t* it = items + (size_t)blockIdx.y * kPageItemInts;
-  const int s = it[0], pg = it[1], row0 = it[2], t0 = it[3] & 255, cnt = it[3] >> 8;
+  int s, pg, row0, t0, cnt;
+  if (items) {
+    const int32_t* it = items + (size_t)blockIdx.y * kPageItemInts;
+    s = it[0]; pg = it[1]; row0 = it[2]; t0 = it[3] & 255; cnt = it[3] >> 8;
+  } else {
+    const int np = round_pages(a.rows_per_seq);
+    s = blockIdx.y / np;
+    const int P = a.pos0[s * a.seq_stride];
+    const int n = a.nrows ? min(a.nrows[s * a.seq_stride], a.rows_per_seq) : a.rows_per_seq;
+    pg = P / kPage + blockIdx.y % np;
+    const int lo = max(P, pg * kPage), hi = min(P + n, (pg + 1) * kPage);
+    if (lo >= hi) return;
+    row0 = s * a.rows_per_seq + lo - P; t0 = lo - pg * kPage; cnt = hi - lo;
+  }
   const int heads_per_layer = a.layer_cols / HD;
   const int layer = blockIdx.x / heads_per_layer, hin = blockIdx.x % heads_per_layer;
   const int qh = a.q_cols / HD, kvh = a.kv_cols / HD;
@@ -710,7 +724,8 @@ __global__ __launch_bounds__(256) void qkv_page_kernel(QkvPostArgs a, const int3
 template <typename T>
 hipError_t qkv_post_pages(const QkvPostArgs& a, const int32_t* items, int n_items, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((a.layer_cols / a.head_dim) * a.n_layers), (unsigned)n_items);
+  const dim3 grid((unsigned)((a.layer_cols / a.head_dim) * a.n_layers),
+                  (unsigned)(items ? n_items : n_items * round_pages(a.rows_per_seq)));
   if (a.head_dim == 128) RT_LAUNCH((qkv_page_kernel<T, 128>), grid, dim3(256), 0, s, a, items);
   else if (a.head_dim == 64) RT_LAUNCH((qkv_page_kernel<T, 64>), grid, dim3(256), 0, s, a, items);
   else return hipErrorInvalidValue;

@@ -376,7 +376,22 @@ static void mid_launch(const GemmArgs& a, int MB, int NB, dim3 grid, hipStream_t
   // x 2560 381 -> 364 us; with one row tile (14B LM head) the 16 waves stay, 3% faster there.
   // The output tile is split spatially, so every element is accumulated over k in the
   // same order either way.
-  if (MB == 128) {
+  //
+  // 33..64 rows: 64-row tiles, 8 waves, six LDS stages.  The copies of the A rows (L2 hits)
+  // and of the weights (HBM) share one in-order queue per compute unit and their times add
+  // (measured per 1 KiB: about 8 ns and 38 ns with all units streaming), so half the A rows
+  // of the 128-row tile show: LM head 151936 x 2560 at 48 rows 147 -> 128 us (6.1 TB/s),
+  // 19456 x 2560 gate|up 30.4 -> 23.6 us, 2560 x 9728 down 15.4 (8 slabs) -> 11.7 (6).
+  if (MB == 64) {
+    if constexpr (AF32) {
+      if (NB == 64) RT_LAUNCH((gemm_mid_kernel<64, 64, 4, true, 8>), grid, dim3(512), 0, s, a);
+      else RT_LAUNCH((gemm_mid_kernel<64, 128, 4, true, 8>), grid, dim3(512), 0, s, a);
+    } else {
+      if (NB == 64) RT_LAUNCH((gemm_mid_kernel<64, 64, 6, false, 8>), grid, dim3(512), 0, s, a);
+      else if (NB == 96) RT_LAUNCH((gemm_mid_kernel<64, 96, 6, false, 8>), grid, dim3(512), 0, s, a);
+      else RT_LAUNCH((gemm_mid_kernel<64, 128, 6, false, 8>), grid, dim3(512), 0, s, a);
+    }
+  } else if (MB == 128) {
     if (NB == 64) RT_LAUNCH((gemm_mid_kernel<128, 64, 4, AF32, 4>), grid, dim3(256), 0, s, a);
     else if (NB == 96) { if constexpr (!AF32) RT_LAUNCH((gemm_mid_kernel<128, 96, 4, false, 8>), grid, dim3(512), 0, s, a); }
     else if (NB == 128) RT_LAUNCH((gemm_mid_kernel<128, 128, 4, AF32, 8>), grid, dim3(512), 0, s, a);
@@ -415,10 +430,16 @@ static double big_step_us(int NB) { return NB == 64 ? 0.40 : NB == 128 ? 0.52 : 
 // rounds x (MB + NB) / 16 x k tiles per slab (slabs cost an extra pass over the
 // output).  Outputs of fewer than 128 tiles take k slabs to fill the chip.  The choices
 // reproduce the fastest measured configuration at the Qwen3-8B and 14B layer shapes.
+static int mid_rows(int M) { return M <= 64 ? 64 : M <= 128 ? 128 : 256; }
+// Relative time of one k tile of a MB x NB workgroup, up to 512 rows: the KiB it copies; at
+// 64 rows a weight KiB counts 4.75 times an A KiB (see mid_launch).
+static double mid_step_cost(int MB, int NB, bool a_f32) {
+  const int ai = (MB / 16) * (a_f32 ? 2 : 1);
+  return ai + (MB == 64 ? 4.75 : 1.0) * (NB / 16);
+}
 struct MidPlan { int NB, ks; };
 static MidPlan mid_plan(const GemmArgs& a, int MB, bool a_f32) {
   const int M = a.e.M, N = a.e.N, KT = a.Kp / kTileK;
-  const int ai = (MB / 16) * (a_f32 ? 2 : 1);
   const size_t slab = (size_t)M * N;
   MidPlan best{64, 1};
   double best_cost = 1e30;
@@ -427,7 +448,8 @@ static MidPlan mid_plan(const GemmArgs& a, int MB, bool a_f32) {
     if ((NB >= 160 || NB == 96) && a_f32) continue;
     if ((NB == 256 && !big) || (NB == 192 && big)) continue;
     if ((NB == 160 || NB == 256) && (MB != 256 || a.e.kind == EPI_PARTIAL)) continue;
-    if (NB == 96 && (MB != 128 || a.e.kind == EPI_PARTIAL)) continue;
+    if (NB == 96 && MB != 64 && (MB != 128 || a.e.kind == EPI_PARTIAL)) continue;
+    if (NB > 128 && MB == 64) continue;
     const long tiles = (long)((N + NB - 1) / NB) * ((M + MB - 1) / MB);
     int ks = 1;
     if (a.e.kind == EPI_PARTIAL) {
@@ -439,9 +461,9 @@ static MidPlan mid_plan(const GemmArgs& a, int MB, bool a_f32) {
       if ((size_t)ks > a.partial_floats / slab) ks = (int)(a.partial_floats / slab);
       if (ks < 1) ks = 1;
     }
-    if ((NB >= 160 || NB == 96) && ks > 1) continue;   // tiles for large outputs only
+    if ((NB >= 160 || (NB == 96 && MB != 64)) && ks > 1) continue;   // tiles for large outputs only
     const double rounds = (double)((tiles * ks + 255) / 256);
-    double cost = rounds * (big ? big_step_us(NB) : (double)(ai + NB / 16)) * ((KT + ks - 1) / ks);
+    double cost = rounds * (big ? big_step_us(NB) : mid_step_cost(MB, NB, a_f32)) * ((KT + ks - 1) / ks);
     // slabs are written and read back once (mostly from cache): a quarter of their
     // bytes relative to the weights'
     if (ks > 1 && a.e.kind != EPI_PARTIAL) cost *= 1.0 + (double)ks * M / (KT * kTileK);
@@ -454,7 +476,7 @@ int gemm_mid_store_slabs(const GemmArgs& a, bool a_f32) {
   GemmArgs g = a;
   if (g.e.kind == EPI_PARTIAL) g.e.kind = EPI_STORE_F32;
   if (g.e.M <= 32) return 1;
-  return mid_plan(g, g.e.M <= 128 ? 128 : 256, a_f32).ks;
+  return mid_plan(g, mid_rows(g.e.M), a_f32).ks;
 }
 
 // Fastest column tile of a GEMM of more than 512 rows with ks slabs (1: any tile).
@@ -472,7 +494,7 @@ static int mid_tile_big(const GemmArgs& a, int ks, bool a_f32) {
 
 int gemm_mid_partial_slabs(const GemmArgs& a, bool a_f32, int max_slabs) {
   if (a.e.M <= 32) return 1;
-  const int MB = a.e.M <= 128 ? 128 : 256;
+  const int MB = mid_rows(a.e.M);
   const bool big = a.e.M > 512;
   GemmArgs g = a;
   g.e.kind = EPI_PARTIAL;
@@ -497,7 +519,7 @@ int gemm_mid_partial_slabs(const GemmArgs& a, bool a_f32, int max_slabs) {
     }
     const MidPlan pl = mid_plan(g, MB, a_f32);
     const long tiles = (long)((g.e.N + pl.NB - 1) / pl.NB) * ((g.e.M + MB - 1) / MB);
-    cost = (double)((tiles * ks + 255) / 256) * ((MB / 16) * (a_f32 ? 2 : 1) + pl.NB / 16) * ((KT + ks - 1) / ks);
+    cost = (double)((tiles * ks + 255) / 256) * mid_step_cost(MB, pl.NB, a_f32) * ((KT + ks - 1) / ks);
     if (cost < best_cost) { best_cost = cost; best = ks; }
   }
   return best;
@@ -506,7 +528,7 @@ int gemm_mid_partial_slabs(const GemmArgs& a, bool a_f32, int max_slabs) {
 hipError_t gemm_mid(const GemmArgs& a, bool a_f32, hipStream_t s) {
   if (!gemm_mid_supports(a)) return hipErrorInvalidValue;
   const int M = a.e.M, N = a.e.N;
-  const int MB = M <= 128 ? 128 : 256;
+  const int MB = mid_rows(M);
   if (a.e.kind == EPI_ARGMAX) {   // the caller sizes its key parts by gemm_mid_cols
     const int NB = gemm_mid_cols(N, M);
     const dim3 grid((N + NB - 1) / NB, (M + MB - 1) / MB, 1);

@@ -14,14 +14,14 @@ template <> struct KeepT<float> { __device__ static float of(float v) { return v
 // and added to the row, which is written back (and optionally captured, packed).  Every
 // load of the row (x, partials, weight) is issued before the first use, so the row costs
 // one memory latency; NP is the partial count when known at compile time (-1: runtime,
-// at most 8), NTH the threads of the workgroup (1024 / NTH chunks per thread).
-template <typename T, typename K, int NP, int NTH>
+// at most 8), NTH the threads of the workgroup, JM the chunks per thread (NTH * JM * 8 >= d).
+template <typename T, typename K, int NP, int NTH, int JM>
 __global__ __launch_bounds__(NTH) void rmsnorm_kernel(float* __restrict__ x, int ldx,
                                                       const T* __restrict__ w, int d, float eps,
                                                       T* __restrict__ out, int ldg, K* keep, int ldk,
                                                       NormFold fold) {
   constexpr int MAXP = NP >= 0 ? NP : 8;
-  constexpr int JM = 1024 / NTH;            // 8-float chunks per thread (d <= 8192)
+  static_assert(NTH * JM * 8 <= 8192, "hidden <= 8192");
   constexpr int NWV = NTH / 64;
   __shared__ float red[NWV];
   const int row = blockIdx.x;
@@ -106,15 +106,21 @@ template <typename T, typename K>
 void rmsnorm(float* x, int ldx, const T* w, int d, float eps, int rows, T* out, int ldg,
              K* keep, int ldk, const NormFold& fold, hipStream_t s) {
   if (rows <= 0) return;
-  // 256 threads with up to four 8-float chunks each; more than four partials (up to 8,
-  // the mid-size kernel's slabs): 1024 threads with one chunk each, so that every load
-  // of a row stays in flight within the register budget
-  if (fold.n_part == 0)
-    RT_LAUNCH((rmsnorm_kernel<T, K, 0, 256>), dim3(rows), dim3(256), 0, s, x, ldx, w, d, eps, out, ldg, keep, ldk, fold);
-  else if (fold.n_part == 4)
-    RT_LAUNCH((rmsnorm_kernel<T, K, 4, 256>), dim3(rows), dim3(256), 0, s, x, ldx, w, d, eps, out, ldg, keep, ldk, fold);
-  else
-    RT_LAUNCH((rmsnorm_kernel<T, K, -1, 1024>), dim3(rows), dim3(1024), 0, s, x, ldx, w, d, eps, out, ldg, keep, ldk, fold);
+#define RT_NORM(NP, NTH, JM) \
+  RT_LAUNCH((rmsnorm_kernel<T, K, NP, NTH, JM>), dim3(rows), dim3(NTH), 0, s, x, ldx, w, d, eps, out, ldg, keep, ldk, fold)
+  // 256 threads with up to four 8-float chunks each; other partial counts (up to 8, the
+  // mid-size kernel's slabs): one chunk per thread, so that every load of a row stays in
+  // flight within the register budget, in the smallest workgroup that covers the row, so
+  // that several rows share a compute unit
+  if (fold.n_part == 0) RT_NORM(0, 256, 4);
+  else if (fold.n_part == 4) RT_NORM(4, 256, 4);
+  else if (d <= 1024) RT_NORM(-1, 128, 1);
+  else if (d <= 2048) RT_NORM(-1, 256, 1);
+  else if (d <= 3072) RT_NORM(-1, 384, 1);
+  else if (d <= 4096) RT_NORM(-1, 512, 1);
+  else if (d <= 5120) RT_NORM(-1, 640, 1);
+  else RT_NORM(-1, 1024, 1);
+#undef RT_NORM
 }
 template void rmsnorm<bf16_t, uint16_t>(float*, int, const bf16_t*, int, float, int, bf16_t*, int,
                                         uint16_t*, int, const NormFold&, hipStream_t);
