@@ -739,7 +739,8 @@ template hipError_t qkv_post_pages<float>(const QkvPostArgs&, const int32_t*, in
 constexpr int kLmTilesPerWave = 2;
 int lmhead_grid(int N) {
   const int tiles = (N + 31) / 32;
-  return (tiles + 4 * kLmTilesPerWave - 1) / (4 * kLmTilesPerWave);
+  const int per = tiles <= 1024 ? 1 : kLmTilesPerWave;   // one tile per wave while that leaves units idle
+  return (tiles + 4 * per - 1) / (4 * per);
 }
 
 // Each wave owns 32-column tiles (two 16-column MFMA tiles) over the full reduction and
