@@ -82,7 +82,7 @@ struct EngineBase {
   hipGraph_t ar_graph = nullptr;       // one target-only step
   hipGraphExec_t ar_gexec = nullptr;
   bool ar_mode = false;                // target-only steps ran since the last prefill
-  int32_t* h_out = nullptr;      // pinned: tokens [R], n [bmax], a [bmax], first [bmax]
+  int32_t* h_out = nullptr;      // pinned: the workspace's out_tok, out_n and out_a (or first tokens)
   // Layer trace (test hook, debug flag 8): the last eager round's intermediates of every
   // drafter and target layer, copied into a device buffer of its own.  One record per
   // layer (drafter layers 0..LD-1, then target layers), then one per pass for the
@@ -199,6 +199,7 @@ struct EngineBase {
   virtual int prefill(int ns, const int32_t* lens, const int32_t* ids, int budget, int32_t* first) = 0;
   virtual int run_round(bool forced) = 0;
   virtual int run_ar_step() = 0;
+  int read_outputs(int32_t* tokens, int32_t* n_comm, int32_t* acc);
   int round(const int32_t* forced, int32_t* tokens, int32_t* n_comm, int32_t* acc);
   int round_static(int32_t* d_tokens, int32_t* d_n_comm, int32_t* d_acc);
   int ar_steps(int n, int32_t* tokens, int32_t* n_gen);
@@ -671,7 +672,6 @@ struct Engine : EngineBase {
   // the chip and streams the weights once.
   int prefill(int ns, const int32_t* lens, const int32_t* ids, int budget, int32_t* first) override {
     const Plan& q = p;
-    drop_graph();
     prefilled = false;
     ar_mode = false;
     PromptTables pt;
@@ -695,6 +695,9 @@ struct Engine : EngineBase {
     HIPCHK(hipMemcpyAsync(h_out, ws + q.first_tok, (size_t)ns * 4, hipMemcpyDeviceToHost, stream));
     HIPCHK(hipStreamSynchronize(stream));
     memcpy(first, h_out, (size_t)ns * 4);
+    // the captured round and step depend on the batch (and the debug flags) only: they read
+    // positions, tokens and counts from the device state
+    if (ns != n_seqs) drop_graph();
     n_seqs = ns;
     prefilled = true;
     return RT_OK;
@@ -921,6 +924,19 @@ int EngineBase::ar_steps(int n, int32_t* tokens, int32_t* n_gen) {
   return RT_OK;
 }
 
+// The round's outputs to the caller: out_tok, out_n and out_a lie one after the other in
+// the workspace and come over in one copy.  Waits for the stream.
+int EngineBase::read_outputs(int32_t* tokens, int32_t* n_comm, int32_t* acc) {
+  const Plan& q = p;
+  const size_t n_off = q.out_n - q.out_tok, a_off = q.out_a - q.out_tok;
+  HIPCHK(hipMemcpyAsync(h_out, ws + q.out_tok, a_off + (size_t)n_seqs * 4, hipMemcpyDeviceToHost, stream));
+  HIPCHK(hipStreamSynchronize(stream));
+  memcpy(tokens, h_out, (size_t)n_seqs * q.bk * 4);
+  memcpy(n_comm, (const char*)h_out + n_off, (size_t)n_seqs * 4);
+  memcpy(acc, (const char*)h_out + a_off, (size_t)n_seqs * 4);
+  return RT_OK;
+}
+
 int EngineBase::round(const int32_t* forced, int32_t* tokens, int32_t* n_comm, int32_t* acc) {
   if (!prefilled) return fail(RT_ERR_STATE, "rt_spec_round called before rt_prefill");
   if (ar_mode) return ar_state_error();
@@ -942,14 +958,7 @@ int EngineBase::round(const int32_t* forced, int32_t* tokens, int32_t* n_comm, i
     CHK(capture_once(graph, gexec, [&] { return run_round(false); }));
     HIPCHK(hipGraphLaunch(gexec, stream));
   }
-  const size_t R = (size_t)n_seqs * q.bk;
-  HIPCHK(hipMemcpyAsync(h_out, ws + q.out_tok, R * 4, hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipMemcpyAsync(h_out + q.R, ws + q.out_n, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipMemcpyAsync(h_out + q.R + q.bmax, ws + q.out_a, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipStreamSynchronize(stream));
-  memcpy(tokens, h_out, R * 4);
-  memcpy(n_comm, h_out + q.R, (size_t)n_seqs * 4);
-  memcpy(acc, h_out + q.R + q.bmax, (size_t)n_seqs * 4);
+  CHK(read_outputs(tokens, n_comm, acc));
   return RT_OK;
 }
 
@@ -1001,14 +1010,7 @@ int EngineBase::profile_round(rt_kernel_stat* stats, double* stage_ms, int32_t* 
   profiling = false;
   launch_events() = LaunchEvents{};
   if (rc != RT_OK) return rc;
-  const size_t R = (size_t)n_seqs * q.bk;
-  HIPCHK(hipMemcpyAsync(h_out, ws + q.out_tok, R * 4, hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipMemcpyAsync(h_out + q.R, ws + q.out_n, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipMemcpyAsync(h_out + q.R + q.bmax, ws + q.out_a, (size_t)n_seqs * 4, hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipStreamSynchronize(stream));
-  memcpy(tokens, h_out, R * 4);
-  memcpy(n_comm, h_out + q.R, (size_t)n_seqs * 4);
-  memcpy(acc, h_out + q.R + q.bmax, (size_t)n_seqs * 4);
+  CHK(read_outputs(tokens, n_comm, acc));
   for (int k = 0; k < RT_K_KINDS; ++k) stats[k] = rt_kernel_stat{k, 0, 0.0, 0.0, 0.0};
   for (const ProfRec& r : prof) {
     float ms = 0.f;
@@ -1338,7 +1340,7 @@ int rt_init_models(const rt_config* cfg, const void* const* weights, int32_t n_w
       if (he != hipSuccess) { delete e; return fail(RT_ERR_HIP, "hipStreamCreate: %s", hipGetErrorString(he)); }
       e->own_stream = true;
     }
-    hipError_t he = hipHostMalloc((void**)&e->h_out, ((size_t)p.R + 3 * (size_t)p.bmax) * 4, hipHostMallocDefault);
+    hipError_t he = hipHostMalloc((void**)&e->h_out, p.out_a - p.out_tok + (size_t)p.bmax * 4, hipHostMallocDefault);
     if (he != hipSuccess) { delete e; return fail(RT_ERR_HIP, "hipHostMalloc: %s", hipGetErrorString(he)); }
     // weights in host memory (pageable or pinned) go through temporary device copies,
     // released once the packing on the stream has finished

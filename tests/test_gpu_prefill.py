@@ -38,3 +38,24 @@ def test_ragged_prompts_in_shared_passes_match_oracle(name, lens):
     assert list(first) == [st.anchor for st in states]
     compare_prefill(eng, R, wl, short, states, tol)
     eng.close()
+
+
+def test_captured_round_serves_later_prefills():
+    """The captured round and target-only step are kept from one prefill to the next of the
+    same batch: results equal a fresh handle's, also after batches of other sizes."""
+    wl = get("mini-bf16-ragged", norm_init="perturbed")
+    W = make_weights(wl)
+    rng = np.random.default_rng(6)
+    sets = [[rng.integers(0, wl.target.vocab // 2, size=n).astype(np.int32) for n in lens]
+            for lens in ((17, 70, 40), (66, 9, 21), (30, 31), (5, 60, 64))]
+    eng = engine_for(wl, W)
+    for prompts in sets:
+        for steps in (False, True):
+            ref = engine_for(wl, W)
+            assert list(eng.prefill(prompts, 30)) == list(ref.prefill(prompts, 30))
+            for _ in range(2):
+                got, want = (eng.ar_steps(3), ref.ar_steps(3)) if steps else (eng.spec_round(), ref.spec_round())
+                for a, b in zip(got, want):
+                    assert np.array_equal(a, b)
+            ref.close()
+    eng.close()
