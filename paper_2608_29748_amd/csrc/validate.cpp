@@ -128,7 +128,9 @@ int make_plan(const rt_config* c, Plan* p) {
   // merge), and at least two 64-key chunks per split at the longest sequence
   auto key_splits = [&](int row_blocks) {
     const int base = q.bmax * q.Hkv * row_blocks;
-    int sp = (256 + base - 1) / base;
+    // (the bf16 kernel of rounds of at most 64 rows fills a compute unit's LDS: a split
+    // too many for 256 units, as 11 x 24 at three sequences, would run after the others)
+    int sp = q.esz == 2 && q.R <= 64 ? 256 / base : (256 + base - 1) / base;
     const int maxsp = ((q.T + 63) / 64) / 2;
     if (sp > maxsp) sp = maxsp;
     if (sp > 64) sp = 64;
