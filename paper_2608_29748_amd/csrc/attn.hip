@@ -1146,74 +1146,91 @@ seg_done:
   }
 }
 
-// One wave per (sequence, kv head, row).  Lane j holds split j's running max and sum;
-// lane l keeps hd elements l*PL .. l*PL+PL-1 of every split's normalised partial row,
-// loaded in batches of 32 splits before the split weights are known, then summed with
-// the weights exp2(m_j - M) * sum_j read from lane j.
+// One wave per (sequence, kv head, row): lane (g, c), g = lane / 16, c = lane % 16, keeps hd
+// elements c*PL .. c*PL+PL-1 of the splits j = g, g+4, g+8, ..; the four lane groups are
+// added at the end.  All NB loads of a batch (NB partial pieces of 16 bytes at hd 128 and
+// their (max, sum) pairs) are in flight together, and every lane weights its own splits by
+// exp2(m_j - M) * sum_j, so nothing is exchanged before the two closing reductions.  (One
+// lane per split's weights, broadcast to 64 lanes of two elements each, took four times
+// the loads and instructions.)
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   using P = typename PartOf<T>::P;
-  constexpr int PL = HD / 64;                 // hd elements per lane (1 or 2)
-  constexpr int NB = 32;                      // splits per batch of loads
-  const int lane = threadIdx.x & 63;
+  constexpr int NB = 8;                       // splits per lane of a batch (32 per wave)
+  constexpr int PL = HD / 16;                 // hd elements per lane
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int rl = blockIdx.x * 4 + (threadIdx.x >> 6);        // row within the row block
   const int s = blockIdx.z / a.row_blocks, rb = blockIdx.z % a.row_blocks, kvh = blockIdx.y;
   const int RBR = a.rb_rows;
   if (rl >= RBR) return;
   const int2 us = attn_unit_slots(a, blockIdx.z);
-  const int S = us.y;                         // <= 64
+  const int S = __builtin_amdgcn_readfirstlane(us.y);   // <= 64: one batch, or two
   const int G = a.n_q_heads / a.n_kv_heads;
   const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
   const int r = rb * RBR + rl;
   if (r >= nq * G) return;
-  const int tok = r / G, h = kvh * G + r % G;
-  T* out = (T*)a.out;
-  const int orow = s * a.rows_per_seq + tok;
-  if (S <= 0) {   // no split holds keys of this unit (not produced by the plans)
-#pragma unroll
-    for (int e = 0; e < PL; ++e) out[pa_index(orow, h * HD + lane * PL + e, a.ldo)] = Elem<T>::from_f32(0.f);
-    return;
-  }
   const size_t blk0 = (size_t)kvh * attn_head_blocks(a) + us.x;
-  const P* opp = reinterpret_cast<const P*>(a.opart) + (blk0 * RBR + rl) * HD + lane * PL;   // split j: + j * RBR * HD
+  const P* opp = reinterpret_cast<const P*>(a.opart) + (blk0 * RBR + rl) * HD + c * PL;   // split j: + j * RBR * HD
   const float* mlp = a.mlpart + (blk0 * RBR + rl) * 2;          // split j: + j * RBR * 2
-  // loads past the last split read split S-1 again (no branch, so all stay in flight);
-  // their weights are zero
+  // loads past the last split read split S-1 (or 0) again, no branch; their weights are zero
   float ob[NB][PL];
+  float2 ml[2][NB];
+  const int last = S > 0 ? S - 1 : 0;
+  auto split_of = [&](int b, int i) { return 4 * NB * b + 4 * i + g; };
+  auto load_ml = [&](int b) {
 #pragma unroll
-  for (int j = 0; j < NB; ++j) PartOf<T>::template load<PL>(opp + (size_t)(j < S ? j : S - 1) * RBR * HD, ob[j]);
-  float mj = -INFINITY, lj = 0.f;
-  if (lane < S) {
-    const float2 v = *reinterpret_cast<const float2*>(mlp + (size_t)lane * RBR * 2);
-    mj = v.x;
-    lj = v.y;
-  }
-  const float M = warp_max(mj);
-  const float f = (M == -INFINITY || mj == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mj - M) * lj;
-  const float den = warp_sum(f);
-  float num[PL];
+    for (int i = 0; i < NB; ++i) {
+      const int j = split_of(b, i);
+      ml[b][i] = *reinterpret_cast<const float2*>(mlp + (size_t)(j < S ? j : last) * RBR * 2);
+    }
+  };
+  auto load_o = [&](int b) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int j = split_of(b, i);
+      PartOf<T>::template load<PL>(opp + (size_t)(j < S ? j : last) * RBR * HD, ob[i]);
+    }
+  };
+  load_ml(0);
+  if (S > 4 * NB) load_ml(1);
+  load_o(0);
+  float M = -INFINITY;
+  auto mask_max = [&](int b) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (split_of(b, i) >= S) ml[b][i].x = -INFINITY;
+      M = fmaxf(M, ml[b][i].x);
+    }
+  };
+  mask_max(0);
+  if (S > 4 * NB) mask_max(1);
+  M = group4_max(M);
+  float den = 0.f, num[PL];
 #pragma unroll
   for (int e = 0; e < PL; ++e) num[e] = 0.f;
+  auto add = [&](int b) {
 #pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const float fj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), j));
+    for (int i = 0; i < NB; ++i) {
+      const float f = ml[b][i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[b][i].x - M) * ml[b][i].y;
+      den += f;
 #pragma unroll
-    for (int e = 0; e < PL; ++e) num[e] += fj * ob[j][e];
-  }
-  for (int j0 = NB; j0 < S; j0 += NB) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      PartOf<T>::template load<PL>(opp + (size_t)(j0 + j < S ? j0 + j : S - 1) * RBR * HD, ob[j]);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const float fj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), j0 + j));
-#pragma unroll
-      for (int e = 0; e < PL; ++e) num[e] += (j0 + j < S ? fj : 0.f) * ob[j][e];
+      for (int e = 0; e < PL; ++e) num[e] += f * ob[i][e];
     }
+  };
+  add(0);
+  if (S > 4 * NB) {
+    load_o(1);
+    add(1);
   }
-  const float inv = den > 0.f ? 1.f / den : 0.f;
+  den = group4_sum(den);
 #pragma unroll
-  for (int e = 0; e < PL; ++e) out[pa_index(orow, h * HD + lane * PL + e, a.ldo)] = Elem<T>::from_f32(num[e] * inv);
+  for (int e = 0; e < PL; ++e) num[e] = group4_sum(num[e]);
+  if (g != 0) return;
+  const int tok = r / G, h = kvh * G + r % G;
+  const float inv = den > 0.f ? 1.f / den : 0.f;   // no split with keys (not produced by the plans): zeros
+  T* out = (T*)a.out + pa_index(s * a.rows_per_seq + tok, h * HD + c * PL, a.ldo);   // PL elements of one 8-element run
+#pragma unroll
+  for (int e = 0; e < PL; ++e) out[e] = Elem<T>::from_f32(num[e] * inv);
 }
 
 // One query tile per wave: 64-row blocks 8 waves with two LDS stages (64 KB at hd 128,
@@ -1355,8 +1372,8 @@ template <typename T>
 hipError_t attention_merge(const AttnArgs& a, hipStream_t s) {
   if (a.splits <= 1) return hipSuccess;
   // few splits (batches): sixteen lanes per row, one batch of loads (8B-shape batch 8:
-  // 7.3 -> 3.5 us, 14B batch 16: 13.6 -> 4.4 us); many splits (batch 1, 32 splits): one
-  // wave per row with all 32 splits' loads in flight at once (3.6 us against 5.8)
+  // 7.3 -> 3.5 us, 14B batch 16: 13.6 -> 4.4 us); more splits (batch 1, 32 splits): one
+  // wave per row, four splits at a time, all loads in flight at once
   if (a.splits <= 8) {
     dim3 grid(kAttnRowsMax / 16, a.n_kv_heads, a.n_seqs * a.row_blocks);
     if (a.head_dim == 128) RT_LAUNCH((attn_merge16_kernel<T, 128>), grid, dim3(256), 0, s, a);
@@ -1364,7 +1381,7 @@ hipError_t attention_merge(const AttnArgs& a, hipStream_t s) {
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
-  dim3 grid(kAttnRowsMax / 4, a.n_kv_heads, a.n_seqs * a.row_blocks);
+  dim3 grid((a.rb_rows + 3) / 4, a.n_kv_heads, a.n_seqs * a.row_blocks);
   if (a.head_dim == 128) RT_LAUNCH((attn_merge_kernel<T, 128>), grid, dim3(256), 0, s, a);
   else if (a.head_dim == 64) RT_LAUNCH((attn_merge_kernel<T, 64>), grid, dim3(256), 0, s, a);
   else return hipErrorInvalidValue;

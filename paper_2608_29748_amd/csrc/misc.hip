@@ -108,18 +108,23 @@ void rmsnorm(float* x, int ldx, const T* w, int d, float eps, int rows, T* out, 
   if (rows <= 0) return;
 #define RT_NORM(NP, NTH, JM) \
   RT_LAUNCH((rmsnorm_kernel<T, K, NP, NTH, JM>), dim3(rows), dim3(NTH), 0, s, x, ldx, w, d, eps, out, ldg, keep, ldk, fold)
-  // 256 threads with up to four 8-float chunks each; other partial counts (up to 8, the
-  // mid-size kernel's slabs): one chunk per thread, so that every load of a row stays in
-  // flight within the register budget, in the smallest workgroup that covers the row, so
-  // that several rows share a compute unit
+#define RT_NORM_D(NP)                     \
+  do {                                    \
+    if (d <= 1024) RT_NORM(NP, 128, 1);   \
+    else if (d <= 2048) RT_NORM(NP, 256, 1); \
+    else if (d <= 3072) RT_NORM(NP, 384, 1); \
+    else if (d <= 4096) RT_NORM(NP, 512, 1); \
+    else if (d <= 5120) RT_NORM(NP, 640, 1); \
+    else RT_NORM(NP, 1024, 1);            \
+  } while (0)
+  // no partials: 256 threads with up to four 8-float chunks each; with partials (4 of the
+  // skinny kernels, up to 8 of the mid-size kernel): one chunk per thread, so that every load
+  // of a row stays in flight within the register budget, in the smallest workgroup that
+  // covers the row, so that several rows share a compute unit
   if (fold.n_part == 0) RT_NORM(0, 256, 4);
-  else if (fold.n_part == 4) RT_NORM(4, 256, 4);
-  else if (d <= 1024) RT_NORM(-1, 128, 1);
-  else if (d <= 2048) RT_NORM(-1, 256, 1);
-  else if (d <= 3072) RT_NORM(-1, 384, 1);
-  else if (d <= 4096) RT_NORM(-1, 512, 1);
-  else if (d <= 5120) RT_NORM(-1, 640, 1);
-  else RT_NORM(-1, 1024, 1);
+  else if (fold.n_part == 4) RT_NORM_D(4);
+  else RT_NORM_D(-1);
+#undef RT_NORM_D
 #undef RT_NORM
 }
 template void rmsnorm<bf16_t, uint16_t>(float*, int, const bf16_t*, int, float, int, bf16_t*, int,
