@@ -702,6 +702,9 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
 
   // this wave's queries: tile t2 (0..NRT-1) column c16 is row row0 + rh*RH + t2*16 + c16
   const int nrt = min(NRT, max(0, (nrows - row0 - rh * RH + 15) / 16));   // tiles with valid rows
+  // keys below this position are visible to all of the wave's rows (prompt passes: up to the
+  // wave's first row itself, whose block may start far before; without a causal mask P)
+  const int mask_from = PROMPT && a.causal ? P + min(row0 + rh * RH, nrows - 1) / G + 1 : P;
   Frag<bf16_t> qf[NRT][NKS];
   int qpos[NRT];
   // Fused q / k post-processing (a.qkv set): every wave takes its q rows from the fp32
@@ -1011,7 +1014,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
       for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
         for (int tau = 0; tau < 2; ++tau) mma(st[tau], kf[tau][ks], qf[t2][ks]);
-      if (kbase + 32 > P) {   // keys that reach the block: causal / end mask
+      if (kbase + 32 > mask_from) {   // keys that reach the block: causal / end mask
 #pragma unroll
         for (int tau = 0; tau < 2; ++tau)
 #pragma unroll
@@ -1253,8 +1256,8 @@ hipError_t attention_partials(const AttnArgs& a, hipStream_t s) {
       // prompt passes: two query tiles per wave, so that each K / V fragment read from LDS
       // serves 32 query rows
       if (!a.blocks) return hipErrorInvalidValue;
-      if (a.head_dim == 128) RT_LAUNCH((attn_bf16_kernel<128, 2, 2, 8, false>), grid, dim3(512), 0, s, a);
-      else if (a.head_dim == 64) RT_LAUNCH((attn_bf16_kernel<64, 2, 2, 8, false>), grid, dim3(512), 0, s, a);
+      if (a.head_dim == 128) RT_LAUNCH((attn_bf16_kernel<128, 4, 2, 8, false>), grid, dim3(512), 0, s, a);
+      else if (a.head_dim == 64) RT_LAUNCH((attn_bf16_kernel<64, 4, 2, 8, false>), grid, dim3(512), 0, s, a);
       else return hipErrorInvalidValue;
     } else if (a.rb_rows == 96) {
       if (a.head_dim == 128 && f) RT_LAUNCH((attn_bf16_kernel<128, 3, 1, 12, true>), grid, dim3(768), 0, s, a);
