@@ -1005,33 +1005,46 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
       const int pg = kh * 2 + (g4 >> 1), h = t * 16 + c16;
       vf[t].v = *reinterpret_cast<const bf16x8*>(sv + pg * PGB + h * 32 + ((g4 & 1) ^ ((h >> 3) & 1)) * 16);
     }
+    // S^T = K Q^T: two 16-key tiles of every query tile, then the scores' maxima.  (A wave
+    // with one valid tile of two computes the second on clamped rows.)
+    f32x4 st[NRT][2];
+    float mxs[NRT];
+    bool raise = false;
 #pragma unroll
     for (int t2 = 0; t2 < NRT; ++t2) {
-      if (t2 >= nrt) break;
-      // S^T = K Q^T: two 16-key tiles of this query tile
-      f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+      st[t2][0] = st[t2][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-        for (int tau = 0; tau < 2; ++tau) mma(st[tau], kf[tau][ks], qf[t2][ks]);
-      if (kbase + 32 > mask_from) {   // keys that reach the block: causal / end mask
+        for (int tau = 0; tau < 2; ++tau) mma(st[t2][tau], kf[tau][ks], qf[t2][ks]);
+    }
+    if (kbase + 32 > mask_from) {   // keys that reach the block: causal / end mask
+      asm volatile("");             // (a branch: most chunks skip it)
+#pragma unroll
+      for (int t2 = 0; t2 < NRT; ++t2)
 #pragma unroll
         for (int tau = 0; tau < 2; ++tau)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int kp = kbase + g4 * 8 + tau * 4 + e;
             const bool vis = kp < kv_end && (!a.causal || kp <= qpos[t2]);
-            st[tau][e] = vis ? st[tau][e] : -INFINITY;
+            st[t2][tau][e] = vis ? st[t2][tau][e] : -INFINITY;
           }
-      }
-      float mx = fmaxf(fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3])),
-                       fmaxf(fmaxf(st[1][0], st[1][1]), fmaxf(st[1][2], st[1][3])));
-      mx = group4_max(mx);
-      const float mxs = mx * sl2;
-      // raise the reference only when a score exceeds it by more than 2^8 (exponentials
-      // stay below 256; the final ratio is unchanged); rescale O and the sum then
-      if (__builtin_amdgcn_ballot_w64(mxs > mref[t2] + 8.f)) {
-        const float mnew = fmaxf(mref[t2], mxs);
+    }
+#pragma unroll
+    for (int t2 = 0; t2 < NRT; ++t2) {
+      float mx = st[t2][0][0];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) mx = __builtin_elementwise_maximum(mx, st[t2][i >> 2][i & 3]);
+      mxs[t2] = group4_max(mx) * sl2;
+      raise |= mxs[t2] > mref[t2] + 8.f;
+    }
+    // raise the reference only when a score exceeds it by more than 2^8 (exponentials
+    // stay below 256; the final ratio is unchanged); rescale O and the sum then
+    if (__builtin_amdgcn_ballot_w64(raise)) {
+#pragma unroll
+      for (int t2 = 0; t2 < NRT; ++t2) {
+        const float mnew = fmaxf(mref[t2], mxs[t2]);
         const float alpha = __builtin_amdgcn_exp2f(mref[t2] - mnew);   // 0 when leaving the sentinel
 #pragma unroll
         for (int t = 0; t < NHT; ++t)
@@ -1040,6 +1053,9 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
         lsum[t2] *= alpha;
         mref[t2] = mnew;
       }
+    }
+#pragma unroll
+    for (int t2 = 0; t2 < NRT; ++t2) {
       const float mr = mref[t2];
       // P as a bf16 high part plus the bf16 rounding of its remainder (about 16
       // significand bits), two MFMAs per tile: the weights entering O are the fp32
@@ -1049,7 +1065,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
       for (int tau = 0; tau < 2; ++tau)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x = __builtin_amdgcn_exp2f(fmaf(st[tau][e], sl2, -mr));
+          const float x = __builtin_amdgcn_exp2f(fmaf(st[t2][tau][e], sl2, -mr));
           lsum[t2] += x;
           const short hb = bf16_bits(x);
           ph.v[tau * 4 + e] = hb;
