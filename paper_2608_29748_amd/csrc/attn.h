@@ -18,8 +18,7 @@ struct AttnArgs {
   int n_q_heads, n_kv_heads, head_dim;
   int splits;                    // key-range splits per (seq, kv head, row block)
   int row_blocks;                // row blocks of rb_rows (token, head) rows per sequence
-  int rb_rows;                   // rows per block: 64, or 96 (bf16) when a sequence has 65..96 rows,
-                                 // or 128 (bf16 prompt passes: `blocks` set)
+  int rb_rows;                   // rows per block: 64, or 96 (bf16) when a sequence has 65..96 rows
   // Prompt passes (one key split): grid.z entry z works on the block
   // blocks[z] = {sequence, activation row of its segment's token 0, tokens of the segment,
   // position of token 0, row block within the segment, 0, 0, 0}; n_blocks of them.  pos0, nq,
@@ -52,7 +51,7 @@ struct AttnArgs {
 // rows (a GQA group of 5 over a 16-token block), so that every KV head is read once.
 constexpr int kAttnRows = 64;
 constexpr int kAttnRowsMax = 96;
-constexpr int kAttnRowsPrompt = 128;   // bf16 prompt passes
+constexpr int kAttnRowsPrompt = 64;   // bf16 prompt passes
 constexpr int kAttnBlockInts = 8;      // int32 per entry of AttnArgs::blocks
 
 // attention = attention_partials (per key split) then attention_merge (splits > 1).
