@@ -354,7 +354,8 @@ struct Engine : EngineBase {
     return gemm_call(kind, A, lda, q.Mrows, false, W, q.d, Kp, c.M, e, k_logical);
   }
 
-  int layer(const char* lw, const LayerCtx& c) {
+  // First half of a decoder layer: input norm, q|k|v, K / V cache rows, attention output.
+  int layer_attn(const char* lw, const LayerCtx& c) {
     const Plan& q = p;
     float* x = at<float>(q.x);
     T* xa = at<T>(q.xa);
@@ -422,7 +423,7 @@ struct Engine : EngineBase {
       const double qio = fuse ? rows * (q.qkvN * 4.0 + 2.0 * q.kvN * sizeof(T)) : rows * q.qN * sizeof(T);
       prof_begin(RT_K_ATTENTION, kvb + qio + rows * q.qN * sizeof(T), 4.0 * keys * c.rows_per_seq * q.Hq * q.hd);
     }
-    HIPCHK(attention_partials<T>(a, stream));
+    if (!c.blocks || c.n_blocks > 0) HIPCHK(attention_partials<T>(a, stream));
     prof_end();
     if (a.splits > 1) {
       // partials: unnormalised O plus (max, sum) per (row, split), read once
@@ -431,12 +432,19 @@ struct Engine : EngineBase {
       prof_end();
     }
     if (fuse) CHK(trace_item(c.trace, TI_Q, at<T>(q.qbuf)));
-    CHK(trace_item(c.trace, TI_ATTN, at<T>(q.attn)));
+    return trace_item(c.trace, TI_ATTN, at<T>(q.attn));
+  }
+
+  int layer(const char* lw, const LayerCtx& c) {
+    const Plan& q = p;
+    float* x = at<float>(q.x);
+    T* xa = at<T>(q.xa);
+    CHK(layer_attn(lw, c));
     CHK(resid_gemm(RT_K_GEMM_O, c, at<T>(q.attn), 16 * q.Kp_q, lw + q.lo_o, q.Kp_q, q.qN, false));
     norm_x((const T*)(lw + q.lo_post), c.M, nullptr, 0);
     CHK(trace_item(c.trace, TI_XMID, x));
     CHK(trace_item(c.trace, TI_H2, xa));
-    e = EpiArgs{};
+    EpiArgs e{};
     e.kind = EPI_SWIGLU; e.out_act = at<T>(q.mlp); e.ldo = 16 * q.Kp_F;
     CHK(gemm_call(RT_K_GEMM_GATE_UP, xa, 16 * q.Kp_d, q.Mrows, false, lw + q.lo_gu, 2 * q.F, q.Kp_d, c.M, e, q.d));
     CHK(trace_item(c.trace, TI_MLP, at<T>(q.mlp)));
@@ -612,8 +620,9 @@ struct Engine : EngineBase {
 
   // Prompt tables of one prefill, as uploaded to pf_tab: the prompts' tokens laid end to
   // end, each sequence's first token index (n_seqs + 1 offsets), and per pass the attention
-  // blocks and page items (int32 offsets into the table).
-  struct PromptPass { int g0, rows, first_end, n_end; size_t blocks, items; int n_blocks, n_items; };
+  // blocks, page items and the attention blocks of the ending sequences' last rows (int32
+  // offsets into the table).
+  struct PromptPass { int g0, rows, first_end, n_end; size_t blocks, items, ends; int n_blocks, n_items, n_ends; };
   struct PromptTables { std::vector<int32_t> tab; size_t off; std::vector<PromptPass> passes; };
   void prompt_tables(int ns, const int32_t* lens, const int32_t* ids, PromptTables* out) const {
     const Plan& q = p;
@@ -660,9 +669,17 @@ struct Engine : EngineBase {
       std::stable_sort(blk.begin(), blk.end(), [](const Blk& x, const Blk& y) { return x.keys > y.keys; });
       ps.blocks = t.size();
       ps.n_blocks = (int)blk.size();
-      for (const Blk& x : blk) {
+      auto put = [&](const Blk& x) {
         const int32_t d[kAttnBlockInts] = {x.s, x.row, x.n, x.pos, x.rb, 0, 0, 0};
         t.insert(t.end(), d, d + kAttnBlockInts);
+      };
+      for (const Blk& x : blk) put(x);
+      // the block of an ending sequence's last query token (all of its heads are in it: a
+      // token's G rows may start in the block before, which then is listed too)
+      ps.ends = t.size();
+      for (const Blk& x : blk) {
+        const int end = x.pos + x.n == lens[x.s] ? x.n * q.G : 0;     // rows of an ending segment
+        if (end > 0 && (x.rb + 1) * rbr > end - q.G) { put(x); ps.n_ends += 1; }
       }
       out->passes.push_back(ps);
     }
@@ -703,12 +720,41 @@ struct Engine : EngineBase {
     return RT_OK;
   }
 
+  // The last target layer of a prompt pass whose output only the ending sequences' last rows
+  // need: their residual rows, updated, go to `last` [n_end][d].  The context append runs
+  // inside (after the input norm, which may still capture the layer before; before `last`
+  // takes its buffer).
+  int tail_layer(const char* lw, const LayerCtx& c, const PromptPass& ps, const int32_t* off, float* last) {
+    const Plan& q = p;
+    const int n = ps.n_end;
+    CHK(layer_attn(lw, c));
+    CHK(context_append(c.M, c.M, nullptr, nullptr, 0, c.pt, c.items, c.n_items));
+    if (n == 0) return RT_OK;
+    T* rows = at<T>(q.qbuf);   // the queries are used up
+    gather_last_packed<T>(at<T>(q.attn), q.qN, 16 * q.Kp_q, off, ps.first_end, n, ps.g0, rows, stream);
+    gather_last(at<float>(q.x), q.d, off, ps.first_end, n, ps.g0, last, stream);
+    EpiArgs e{};
+    e.kind = EPI_RESID; e.resid = last; e.ldr = q.d;
+    CHK(gemm_call(RT_K_GEMM_O, rows, 16 * q.Kp_q, q.Mrows, false, lw + q.lo_o, q.d, q.Kp_q, n, e, q.qN));
+    rmsnorm<T, K>(last, q.d, (const T*)(lw + q.lo_post), q.d, cfg.rms_eps, n, at<T>(q.xa), 16 * q.Kp_d, nullptr, 0,
+                  NormFold{}, stream);
+    EpiArgs g{};
+    g.kind = EPI_SWIGLU; g.out_act = at<T>(q.mlp); g.ldo = 16 * q.Kp_F;
+    CHK(gemm_call(RT_K_GEMM_GATE_UP, at<T>(q.xa), 16 * q.Kp_d, q.Mrows, false, lw + q.lo_gu, 2 * q.F, q.Kp_d, n, g, q.d));
+    return gemm_call(RT_K_GEMM_DOWN, at<T>(q.mlp), 16 * q.Kp_F, q.Mrows, false, lw + q.lo_down, q.d, q.Kp_F, n, e, q.F);
+  }
+
   int prompt_pass(const PromptPass& ps, const int32_t* tab, const int32_t* off, const int32_t* ptab, int rbr,
                   int budget) {
     const Plan& q = p;
     const int n = ps.rows;
     const int32_t* items = tab + ps.items;
     embed_rows<T>(at<T>(q.embed), q.d, tab + ps.g0, n, at<float>(q.x), q.d, stream);
+    // The last layer's output is needed for the last rows of the ending sequences only,
+    // unless the drafter's context reads it: its keys and values are computed for every row,
+    // the rest of it for those rows (one of 36 layers of the 4B shape: about 0.9 of 43 ms).
+    const bool tail = cond_slot(q.L - 1) < 0;
+    float* last = at<float>(q.fcout);
     for (int l = 0; l < q.L; ++l) {
       const int slot = cond_slot(l);
       LayerCtx c{n, n, 1, 0, 1, 1, 1, rbr, nullptr, nullptr, ptab,
@@ -716,12 +762,16 @@ struct Engine : EngineBase {
                  slot >= 0 ? at<T>(q.g) : nullptr, slot * q.d, nullptr, l + 1 < q.L};
       c.blocks = tab + ps.blocks; c.n_blocks = ps.n_blocks;
       c.items = items; c.n_items = ps.n_items;
-      CHK(layer(tlayer(l), c));
+      if (tail && l + 1 == q.L) {
+        c.blocks = tab + ps.ends; c.n_blocks = ps.n_ends;
+        CHK(tail_layer(tlayer(l), c, ps, off, last));
+      } else {
+        CHK(layer(tlayer(l), c));
+      }
     }
-    CHK(context_append(n, n, nullptr, nullptr, 0, ptab, items, ps.n_items));
+    if (!tail) CHK(context_append(n, n, nullptr, nullptr, 0, ptab, items, ps.n_items));
     if (ps.n_end > 0) {   // first tokens of the sequences whose prompts end in this pass
-      float* last = at<float>(q.fcout);
-      gather_last(at<float>(q.x), q.d, off, ps.first_end, ps.n_end, ps.g0, last, stream);
+      if (!tail) gather_last(at<float>(q.x), q.d, off, ps.first_end, ps.n_end, ps.g0, last, stream);
       rmsnorm<T, K>(last, q.d, at<T>(q.t_final_norm), q.d, cfg.rms_eps, ps.n_end, at<T>(q.xa), 16 * q.Kp_d, nullptr, 0,
                     NormFold{}, stream);
       const bool smp = sampling();

@@ -79,6 +79,9 @@ void first_tokens(int32_t* state, int seq0, int n, const uint64_t* keys, const i
 // out[i] = row off[seq0+i+1] - 1 - g0 of x: the last prompt rows of n consecutive sequences
 // within a pass that starts at token g0 of the concatenated prompts.
 void gather_last(const float* x, int d, const int32_t* off, int seq0, int n, int g0, float* out, hipStream_t s);
+// The same rows of a packed GEMM operand of width K (group stride ldg) into rows 0..n-1 of out.
+template <typename T>
+void gather_last_packed(const T* a, int K, int ldg, const int32_t* off, int seq0, int n, int g0, T* out, hipStream_t s);
 void fill_zero(void* p, size_t bytes, hipStream_t s);
 // Plain read of bytes (a multiple of 16) at p by `grid` workgroups of 256 threads.
 void stream_read(const void* p, size_t bytes, int grid, uint32_t* sink, hipStream_t s);

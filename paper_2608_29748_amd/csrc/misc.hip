@@ -428,6 +428,24 @@ void gather_last(const float* x, int d, const int32_t* off, int seq0, int n, int
   RT_LAUNCH(gather_last_kernel, dim3(n), dim3(256), 0, s, x, d, off, seq0, g0, out);
 }
 
+template <typename T>
+__global__ void gather_last_packed_kernel(const T* __restrict__ a, int K, int ldg, const int32_t* __restrict__ off,
+                                          int seq0, int g0, T* __restrict__ out) {
+  const int row = off[seq0 + blockIdx.x + 1] - 1 - g0;
+  for (int k = 8 * threadIdx.x; k < K; k += 8 * blockDim.x) {   // 8-element runs
+    Frag<T> f;
+    f.load(a + pa_index(row, k, ldg));
+    f.store(out + pa_index(blockIdx.x, k, ldg));
+  }
+}
+template <typename T>
+void gather_last_packed(const T* a, int K, int ldg, const int32_t* off, int seq0, int n, int g0, T* out, hipStream_t s) {
+  if (n <= 0) return;
+  RT_LAUNCH((gather_last_packed_kernel<T>), dim3(n), dim3(256), 0, s, a, K, ldg, off, seq0, g0, out);
+}
+template void gather_last_packed<bf16_t>(const bf16_t*, int, int, const int32_t*, int, int, int, bf16_t*, hipStream_t);
+template void gather_last_packed<float>(const float*, int, int, const int32_t*, int, int, int, float*, hipStream_t);
+
 __global__ void fill_zero_kernel(uint4* p, size_t n16) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
     p[i] = make_uint4(0, 0, 0, 0);

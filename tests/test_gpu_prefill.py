@@ -11,31 +11,47 @@ from gpu_parity import compare_prefill, engine_for, log
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("name,lens", [
-    ("mini-bf16", (1, 15, 16, 17, 255, 1500, 130, 2300, 33)),    # two passes, cut inside a page
-    ("mini-bf16-gqa5", (700, 3500, 20)),                          # hd 128, 128-row blocks of 25.6 tokens
-    ("mini-bf16-odd", (40, 21, 500, 80)),                         # 641 rows: k slabs above 512 rows
-    ("mini-bf16-b4", (600, 2, 1, 900)),                           # slabs folded by the norm, 1503 rows
-    ("tiny-f32", (3, 2000, 2100, 40)),                            # fp32 kernels, two passes
+def check_first(first, R, prompts, states, tol):
+    """First tokens: the oracle's, or at a near-tie one whose oracle logit is within 2 tol of
+    the largest (each logit may be off by tol)."""
+    for f, p, st in zip(first, prompts, states):
+        if int(f) != st.anchor:
+            z = R.m.target_forward(R.m.new_state(p, 4), p, 0).logits[-1]
+            assert z[int(f)] >= z[st.anchor] - 2 * tol, (int(f), st.anchor)
+
+
+@pytest.mark.parametrize("name,lens,cond", [
+    ("mini-bf16", (1, 15, 16, 17, 255, 1500, 130, 2300, 33), None),    # two passes, cut inside a page
+    ("mini-bf16-gqa5", (700, 3500, 20), None),                          # hd 128, blocks of 12.8 tokens
+    ("mini-bf16-odd", (40, 21, 500, 80), None),                         # 641 rows: k slabs above 512 rows
+    ("mini-bf16-b4", (600, 2, 1, 900), None),                           # slabs folded by the norm, 1503 rows
+    ("tiny-f32", (3, 2000, 2100, 40), None),                            # fp32 kernels, two passes
+    # the drafter does not read the last layer: it runs for the ending sequences' last rows
+    ("mini-bf16", (1, 15, 16, 17, 255, 1500, 130, 2300, 33), (0, 1)),   # its input norm captures layer 1
+    ("mini-bf16-gqa5", (4500, 20, 51), (0,)),                           # a first pass in which none ends
+    ("mini-bf16-b4", tuple(range(5, 45)), (0,)),                        # forty ending rows
+    ("tiny-f32", (3, 2000, 2100, 40), (0,)),
 ])
-def test_ragged_prompts_in_shared_passes_match_oracle(name, lens):
+def test_ragged_prompts_in_shared_passes_match_oracle(name, lens, cond):
     wl = get(name, norm_init="perturbed", batch=len(lens), prompt_len=(min(lens), max(lens)), new_tokens=12)
+    if cond is not None:
+        wl = wl.with_(cond_layers=cond)
     W = make_weights(wl)
     rng = np.random.default_rng(5)
     prompts = [rng.integers(0, wl.target.vocab // 2, size=n).astype(np.int32) for n in lens]
     eng = engine_for(wl, W)
     R = OracleRunner(OracleModel(wl, W))
+    tol = {"f32": 1e-4, "bf16": 2e-2}[wl.dtype]
     first = eng.prefill(prompts, wl.new_tokens)
     states = [R.prefill(p, wl.new_tokens) for p in prompts]
-    assert list(first) == [st.anchor for st in states]
-    tol = {"f32": 1e-4, "bf16": 2e-2}[wl.dtype]
+    check_first(first, R, prompts, states, tol)
     rep = compare_prefill(eng, R, wl, prompts, states, tol)
-    log(f"[{name} {lens}] prefill max err {rep.max_err}")
+    log(f"[{name} {len(lens)} prompts] prefill max err {rep.max_err}")
     # a second, shorter prefill on the same handle: stale rows of the first stay unseen
     short = [p[: max(1, len(p) // 3)] for p in prompts[::-1]]
     first = eng.prefill(short, wl.new_tokens)
     states = [R.prefill(p, wl.new_tokens) for p in short]
-    assert list(first) == [st.anchor for st in states]
+    check_first(first, R, short, states, tol)
     compare_prefill(eng, R, wl, short, states, tol)
     eng.close()
 
