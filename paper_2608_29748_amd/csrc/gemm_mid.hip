@@ -419,10 +419,13 @@ static void mid_launch(const GemmArgs& a, int MB, int NB, dim3 grid, hipStream_t
 
 // More than 512 rows (prompt passes): microseconds per 32-wide k tile of one round of 256
 // workgroups, measured with the chip full (K = 2560..17408, 1024..4096 rows; e.g. 4096 x
-// 19456 x 2560: 256 columns 364 us, 160 400, 128 407; 4096 x 2560 x 9728: 160 columns
-// (256 workgroups) 172 us, 256 213, 128 263).  The rounds decide: the widest tile moves
-// the fewest LDS bytes per MFMA, a narrower one may fill the last round.
-static double big_step_us(int NB) { return NB == 64 ? 0.40 : NB == 128 ? 0.52 : NB == 160 ? 0.60 : 0.85; }
+// 19456 x 2560: 256 columns 371 us, 192 399, 160 407, 128 430; 4096 x 2560 x 9728: 160
+// columns (256 workgroups) 171 us, 192 184, 256 231, 128 263; 4096 x 6144 x 2560: 192
+// columns (512 workgroups) 110 us, 128 116, 256 130).  The rounds decide: the widest tile
+// moves the fewest LDS bytes per MFMA, a narrower one may fill the last round.
+static double big_step_us(int NB) {
+  return NB == 64 ? 0.40 : NB == 128 ? 0.52 : NB == 160 ? 0.61 : NB == 192 ? 0.70 : 0.88;
+}
 
 // Tile width and k slabs, up to 512 rows.  A workgroup streams (MB + NB) / 16 KiB through LDS per k
 // tile, about one workgroup per compute unit is resident for the wide tiles, and the
@@ -446,8 +449,8 @@ static MidPlan mid_plan(const GemmArgs& a, int MB, bool a_f32) {
   const bool big = M > 512;
   for (int NB : {64, 96, 128, 160, 192, 256}) {
     if ((NB >= 160 || NB == 96) && a_f32) continue;
-    if ((NB == 256 && !big) || (NB == 192 && big)) continue;
-    if ((NB == 160 || NB == 256) && (MB != 256 || a.e.kind == EPI_PARTIAL)) continue;
+    if (NB == 256 && !big) continue;
+    if ((NB == 160 || NB == 256 || (NB == 192 && big)) && (MB != 256 || a.e.kind == EPI_PARTIAL)) continue;
     if (NB == 96 && MB != 64 && (MB != 128 || a.e.kind == EPI_PARTIAL)) continue;
     if (NB > 128 && MB == 64) continue;
     const long tiles = (long)((N + NB - 1) / NB) * ((M + MB - 1) / MB);
@@ -483,7 +486,7 @@ int gemm_mid_store_slabs(const GemmArgs& a, bool a_f32) {
 static int mid_tile_big(const GemmArgs& a, int ks, bool a_f32) {
   int best = 64;
   double best_cost = 1e30;
-  for (int NB : {64, 128, 160, 256}) {
+  for (int NB : {64, 128, 160, 192, 256}) {
     if (NB > 128 && (a_f32 || ks > 1)) continue;
     const long tiles = (long)((a.e.N + NB - 1) / NB) * ((a.e.M + 255) / 256);
     const double cost = (double)((tiles * ks + 255) / 256) * big_step_us(NB);
