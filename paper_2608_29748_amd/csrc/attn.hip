@@ -1188,13 +1188,21 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
   const int r = rb * RBR + rl;
   if (r >= nq * G) return;
+  const int tok = r / G, h = kvh * G + r % G;
+  T* out = (T*)a.out + pa_index(s * a.rows_per_seq + tok, h * HD + c * PL, a.ldo);   // PL elements of one 8-element run
+  if (S <= 0) {   // no split holds keys of this unit (not produced by the plans)
+    if (g == 0)
+#pragma unroll
+      for (int e = 0; e < PL; ++e) out[e] = Elem<T>::from_f32(0.f);
+    return;
+  }
   const size_t blk0 = (size_t)kvh * attn_head_blocks(a) + us.x;
   const P* opp = reinterpret_cast<const P*>(a.opart) + (blk0 * RBR + rl) * HD + c * PL;   // split j: + j * RBR * HD
   const float* mlp = a.mlpart + (blk0 * RBR + rl) * 2;          // split j: + j * RBR * 2
-  // loads past the last split read split S-1 (or 0) again, no branch; their weights are zero
+  // loads past the last split read split S-1 again, no branch; their weights are zero
   float ob[NB][PL];
   float2 ml[2][NB];
-  const int last = S > 0 ? S - 1 : 0;
+  const int last = S - 1;
   auto split_of = [&](int b, int i) { return 4 * NB * b + 4 * i + g; };
   auto load_ml = [&](int b) {
 #pragma unroll
@@ -1245,9 +1253,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 #pragma unroll
   for (int e = 0; e < PL; ++e) num[e] = group4_sum(num[e]);
   if (g != 0) return;
-  const int tok = r / G, h = kvh * G + r % G;
-  const float inv = den > 0.f ? 1.f / den : 0.f;   // no split with keys (not produced by the plans): zeros
-  T* out = (T*)a.out + pa_index(s * a.rows_per_seq + tok, h * HD + c * PL, a.ldo);   // PL elements of one 8-element run
+  const float inv = den > 0.f ? 1.f / den : 0.f;
 #pragma unroll
   for (int e = 0; e < PL; ++e) out[e] = Elem<T>::from_f32(num[e] * inv);
 }

@@ -341,17 +341,19 @@ int gemm_mid_cols(int N, int M) {
   return N / 128 >= 160 ? 128 : 64;
 }
 
-bool gemm_mid_supports(const GemmArgs& a) {
-  const int k = a.e.kind;
-  if (a.e.M <= 32) return false;
-  if (k == EPI_PARTIAL) return a.ksplit >= 1;
-  return a.ksplit == 1;
-}
-
 // The register epilogue covers these kinds; the others always take the slab path.
 static bool mid_direct_kind(int k) {
   return k == EPI_STORE_F32 || k == EPI_STORE_ACT || k == EPI_RESID || k == EPI_SWIGLU || k == EPI_PARTIAL ||
          k == EPI_ARGMAX;
+}
+
+bool gemm_mid_supports(const GemmArgs& a) {
+  const int k = a.e.kind;
+  if (a.e.M <= 32) return false;
+  // the slab path needs room for one slab at least
+  if (!mid_direct_kind(k) && (!a.partial || a.partial_floats < (size_t)a.e.M * a.e.N)) return false;
+  if (k == EPI_PARTIAL) return a.ksplit >= 1;
+  return a.ksplit == 1;
 }
 
 template <bool AF32>
