@@ -55,10 +55,16 @@ DOMINANT = "gemm_gate_up"
 REPLAY_KINDS = (0, 1, 2, 3, 4, 5, 6, 7, 10)   # GEMM classes, attention, merge, LM head
 
 
+def gate_up_mid(wl):
+    """Whether a round's gate|up GEMM runs on the mid-size kernel."""
+    rows = wl.batch * wl.block_size
+    return rows > 64 or (rows > 32 and wl.dtype == "bf16" and 2 * wl.target.ffn >= 128 * 96)
+
+
 def dominant_desc(wl):
     """The dominant kernel's launch class at this workload's verify shape."""
     rows = wl.batch * wl.block_size
-    kern = "gemm16_kernel" if rows <= 64 else "gemm_mid_kernel"
+    kern = "gemm_mid_kernel" if gate_up_mid(wl) else "gemm16_kernel"
     # at most 16 bf16 rows, K <= 2560 and at least 16384 columns: the k-slab kernel with
     # the activation block staged in LDS (one slab)
     if rows <= 16 and wl.dtype == "bf16" and wl.target.hidden <= 2560 and 2 * wl.target.ffn >= 16384:
@@ -74,8 +80,8 @@ MID_SOURCES = GEMM_SOURCES + ("paper_2608_29748_amd/csrc/gemm_mid.hip",)
 
 def traffic_sources(wl):
     """The sources a traffic record of the dominant GEMM depends on: the mid-size kernel
-    (more than 64 rows per round) adds its own file."""
-    return MID_SOURCES if wl.batch * wl.block_size > 64 else GEMM_SOURCES
+    (see gate_up_mid) adds its own file."""
+    return MID_SOURCES if gate_up_mid(wl) else GEMM_SOURCES
 
 
 def gemm_source_hash(sources=GEMM_SOURCES) -> str:

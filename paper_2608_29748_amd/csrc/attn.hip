@@ -12,6 +12,9 @@
 // per chunk.  fp32 storage (small configurations): chunks are staged through
 // registers.
 //
+// Prompt passes (bf16) run the same kernel over a list of blocks, several sequences in one
+// grid, without key splits.
+//
 // In rounds and target-only steps (bf16, at most 16 rows per sequence) the same kernel
 // also applies the per-head q / k RMSNorm and RoPE to the fp32 q|k|v projection and
 // writes the block's K / V rows to the caches (a launch fewer per layer); it rounds
@@ -526,9 +529,10 @@ __device__ __forceinline__ int kswz(int r, int pg) { return (r ^ ((pg & 1) << 2)
 // Work split of a workgroup of NW waves: wave w owns query rows rh*16*NRT .. +16*NRT-1
 // of the row block (rh = w/2, NRT 16-row MFMA tiles) and keys kh*32..kh*32+31 of every
 // 64-key chunk (kh = w%2, two pages); the two key halves of the same rows are merged
-// through LDS at the end.  Every K / V byte staged in LDS is read by NW/2 waves.  The
-// launches use one query tile per wave (8 or 12 waves): two or three waves per SIMD then
-// interleave their dependent chains (LDS reads, score MFMAs, online softmax, PV MFMAs).
+// through LDS at the end.  Every K / V byte staged in LDS is read by NW/2 waves.  Rounds
+// use one query tile per wave (8 or 12 waves): two or three waves per SIMD then interleave
+// their dependent chains (LDS reads, score MFMAs, online softmax, PV MFMAs).  Prompt passes
+// use two tiles per wave (NRT = 2, four waves, two workgroups per compute unit).
 //
 // Key order inside a wave's 32 keys: score tile tau (0, 1), A-operand row m holds key
 // (m/4)*8 + 4*tau + m%4, so that the accumulator lane (g, q) ends up with the eight
