@@ -334,6 +334,15 @@ int rt_debug_read_rows(rt_model* m, int32_t tensor_id, int32_t seq, int32_t pos0
  * computed elsewhere). */
 int rt_debug_write(rt_model* m, int32_t tensor_id, int32_t seq, const void* host_src, size_t bytes);
 
+/* What the library would launch for n_seqs sequences of a configuration; needs no model and
+ * no GPU, so that tests can check that a size reaches the form it is meant for.  Returns a
+ * negative RT_ERR_* code for an invalid argument. */
+enum {
+  RT_C_ATTN_SLOTS = 0      /* workgroups per KV head of the attention of a round (arg = block_size)
+                              or a target-only step (arg = 1) */
+};
+int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n_seqs, int32_t arg);
+
 #ifdef __cplusplus
 }
 #endif

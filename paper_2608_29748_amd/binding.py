@@ -40,13 +40,14 @@ RT_T_TRACE_TARGET_Q, RT_T_TRACE_TARGET_ATTN, RT_T_TRACE_TARGET_XMID, RT_T_TRACE_
 RT_K_KINDS = 12
 KERNEL_KIND_NAMES = ["gemm_qkv", "gemm_o", "gemm_gate_up", "gemm_down", "gemm_context", "gemm_cond",
                      "attention", "attn_merge", "rmsnorm", "qkv_post", "lm_head", "misc"]
+RT_C_ATTN_SLOTS = 0
 STAGE_NAMES = ["condition", "draft", "draft_lm_head", "verify", "verify_lm_head", "accept", "context_append"]
 RT_PROF_STAGES = 7
 
 EXPORTS = ["rt_workspace_bytes", "rt_weight_count", "rt_init_models", "rt_prefill", "rt_spec_round",
            "rt_destroy", "rt_last_error", "rt_set_debug", "rt_spec_round_forced", "rt_debug_read",
            "rt_debug_write", "rt_profile_round", "rt_time_kernel", "rt_ar_steps", "rt_debug_read_rows",
-           "rt_spec_round_static", "rt_stream_read", "rt_weight_elements"]
+           "rt_spec_round_static", "rt_stream_read", "rt_weight_elements", "rt_debug_choice"]
 
 
 class RetraceError(RuntimeError):
@@ -110,10 +111,11 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
     lib.rt_profile_round.argtypes = [P, C.POINTER(rt_kernel_stat), C.POINTER(C.c_double), i32p, i32p, i32p]
     lib.rt_time_kernel.argtypes = [P, C.c_int32, C.c_int32, C.POINTER(rt_kernel_stat)]
     lib.rt_ar_steps.argtypes = [P, C.c_int32, i32p, i32p]
+    lib.rt_debug_choice.argtypes = [C.POINTER(rt_config), C.c_int32, C.c_int32, C.c_int32]
     for name in ("rt_init_models", "rt_prefill", "rt_spec_round", "rt_spec_round_forced", "rt_spec_round_static",
                  "rt_stream_read", "rt_destroy",
                  "rt_set_debug", "rt_debug_read", "rt_debug_read_rows", "rt_debug_write", "rt_profile_round",
-                 "rt_time_kernel", "rt_ar_steps"):
+                 "rt_time_kernel", "rt_ar_steps", "rt_debug_choice"):
         getattr(lib, name).restype = C.c_int
     return lib
 
@@ -262,6 +264,14 @@ def rt_debug_read_rows(h: int, tensor_id: int, seq: int, pos0: int, nbytes: int)
 def rt_debug_write(h: int, tensor_id: int, seq: int, data: bytes) -> None:
     buf = C.create_string_buffer(data, len(data))
     _check(_lib.rt_debug_write(C.c_void_p(h), tensor_id, seq, buf, len(data)))
+
+
+def rt_debug_choice(cfg: rt_config, choice: int, n_seqs: int, arg: int) -> int:
+    """What the library would launch (RT_C_*) for n_seqs sequences; needs no GPU."""
+    v = _lib.rt_debug_choice(C.byref(cfg), choice, n_seqs, arg)
+    if v < 0:
+        _check(v)
+    return v
 
 
 def rt_destroy(h: int) -> None:

@@ -17,6 +17,7 @@ struct AttnArgs {
   int causal;                    // 1: key position <= query position; 0: every key below pos0+nq
   int n_q_heads, n_kv_heads, head_dim;
   int splits;                    // key-range splits per (seq, kv head, row block)
+  int slots, fit;                // workgroups per KV head, and those of one pass of the chip: see attn_slots
   int row_blocks;                // row blocks of rb_rows (token, head) rows per sequence
   int rb_rows;                   // rows per block: 64, or 96 (bf16) when a sequence has 65..96 rows
   // Prompt passes (one key split): grid.z entry z works on the block
@@ -53,6 +54,18 @@ constexpr int kAttnRows = 64;
 constexpr int kAttnRowsMax = 96;
 constexpr int kAttnRowsPrompt = 64;   // bf16 prompt passes
 constexpr int kAttnBlockInts = 8;      // int32 per entry of AttnArgs::blocks
+
+// Splits per unit, workgroups (slots) per KV head and, for the balanced plan, the slots per KV
+// head that 256 compute units take in one pass, for a launch over n_units (sequence, row block)
+// units.  `splits` is the handle's count, about one workgroup per compute unit at max_batch,
+// rounded up.  `one_pass` (bf16 handles of at most 64 round rows): workgroups past 256 make the
+// launch longer, as a unit that has two runs both slower or one after the other (three
+// sequences x 16 rows, 11 splits against 10: 76 and 56 us of attention a round at head_dim 64;
+// x 20 rows at head_dim 128 158 and 90), so a launch gets 256 / n_kv_heads slots a head where
+// that is two or more a unit.  Below two a unit it keeps the full count and the balanced plan
+// decides from the contexts how many to use.  Unbalanced launches take whole splits per unit.
+struct AttnSlots { int splits, slots, fit; };
+AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass);
 
 // attention = attention_partials (per key split) then attention_merge (splits > 1).
 template <typename T>

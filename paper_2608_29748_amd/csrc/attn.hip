@@ -67,14 +67,16 @@ extern "C" __device__ int __ockl_wfred_max_i32(int);
 extern "C" __device__ int __ockl_wfscan_add_i32(int, bool);
 
 // Key splits.  A work unit is one (sequence, row block), u = seq * row_blocks + rb; the
-// workgroups of one KV head are slots 0 .. n_units * splits - 1 (slot = blockIdx.z *
-// splits + blockIdx.x), and the partials of slot x of KV head h sit at block
+// workgroups of one KV head are slots 0 .. a.slots - 1 (slot = blockIdx.z * splits +
+// blockIdx.x; a.slots is n_units * splits, or fewer where the balanced plan may share fewer
+// out, see attn_slots), and the partials of slot x of KV head h sit at block
 // h * n_slots + x.  Uniform plan: unit u owns slots u*splits .. u*splits + splits-1.
 // Balanced plan (2..64 units and splits > 1), for batches of unequal context lengths:
 // unit u owns s_u = ceil(n_u / q) consecutive slots, n_u being its number of 64-key
-// chunks and q the smallest chunk count per split for which the s_u fit in the slots.
-// q never exceeds the uniform plan's ceil(max n_u / splits), so no split is longer than
-// under the uniform plan, and s_u <= 64 (one merge lane per split).  Every wave derives
+// chunks and q the smallest chunk count per split for which the s_u fit in the slots (see
+// attn_balanced_plan for launches of more slots than one pass of the chip).
+// q never exceeds ceil(max n_u / floor(slots / units)), so no split is longer than
+// under a uniform plan of these slots, and s_u <= 64 (one merge lane per split).  Every wave derives
 // the plan from the sequence lengths; the workgroup of slot 0 of KV head 0 stores it
 // for the merge, which runs after the partial kernel on the same stream.
 __device__ __forceinline__ bool attn_balanced(const AttnArgs& a) {
@@ -100,18 +102,31 @@ struct SplitPlan {
 // Balanced plan; all 64 lanes of the wave must be active.
 __device__ __forceinline__ SplitPlan attn_balanced_plan(const AttnArgs& a, int rbr) {
   const int lane = threadIdx.x & 63;
-  const int nu = a.n_seqs * a.row_blocks, slots = nu * a.splits;
+  const int nu = a.n_seqs * a.row_blocks;
   const int n = lane < nu ? attn_unit_chunks(a, lane, rbr) : 0;
   const int tot = __ockl_wfred_add_i32(n), mx = __ockl_wfred_max_i32(n);
-  int lo = max(1, max((tot + slots - 1) / slots, (mx + 63) / 64));
-  int hi = max(lo, (mx + a.splits - 1) / a.splits);
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (__ockl_wfred_add_i32((n + mid - 1) / mid) <= slots) hi = mid;
-    else lo = mid + 1;
+  // the smallest chunk count per split for which the splits fit `slots` (at least one a unit)
+  auto bound = [&](int slots) {
+    const int each = slots / nu;
+    int lo = max(1, max((tot + slots - 1) / slots, (mx + 63) / 64));
+    int hi = max(lo, (mx + each - 1) / each);
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (__ockl_wfred_add_i32((n + mid - 1) / mid) <= slots) hi = mid;
+      else lo = mid + 1;
+    }
+    return lo;
+  };
+  int q = bound(a.fit);
+  if (a.slots > a.fit) {
+    // more than one pass of the chip where that is shorter, as with one long context among
+    // short ones: two passes, or, where a unit holds two workgroups (64 rows at head_dim 64,
+    // 98 VGPRs and 74 KB), about 5/3 of a pass
+    const int q2 = bound(a.slots);
+    if (a.head_dim == 64 && rbr == 64 ? 5 * q2 < 3 * q : 2 * q2 < q) q = q2;
   }
-  const int cnt = (n + lo - 1) / lo;
-  return SplitPlan{cnt, __ockl_wfscan_add_i32(cnt, true), lo};
+  const int cnt = (n + q - 1) / q;
+  return SplitPlan{cnt, __ockl_wfscan_add_i32(cnt, true), q};
 }
 // Sequence, row block, query tokens, first position and first activation row of a unit:
 // an entry of the block list (prompt passes, one split) or (sequence, row block).
@@ -149,8 +164,7 @@ __device__ __forceinline__ bool attn_slot_work(const AttnArgs& a, int rbr, int& 
 // Partial blocks per KV head: one per slot, plus one per unit boundary under the
 // balanced plans (a spanning slot writes one block per unit it meets).
 __device__ __forceinline__ int attn_head_blocks(const AttnArgs& a) {
-  const int nu = a.n_seqs * a.row_blocks, slots = nu * a.splits;
-  return attn_balanced(a) ? slots + nu - 1 : slots;
+  return attn_balanced(a) ? a.slots + a.n_seqs * a.row_blocks - 1 : a.slots;
 }
 // First partial block (x) and split count (y) of unit u (merge side): the balanced plan
 // as the partial kernel's first workgroup stored it, clamped to this launch's blocks (a
@@ -177,7 +191,7 @@ struct SpanPlan {
 };
 __device__ __forceinline__ SpanPlan attn_span_plan(const AttnArgs& a, int rbr) {
   const int lane = threadIdx.x & 63;
-  const int nu = a.n_seqs * a.row_blocks, S = nu * a.splits;
+  const int nu = a.n_seqs * a.row_blocks, S = a.slots;
   SpanPlan p;
   p.n = lane < nu ? attn_unit_chunks(a, lane, rbr) : 0;
   p.start = __ockl_wfscan_add_i32(p.n, true) - p.n;
@@ -388,7 +402,7 @@ __global__ __launch_bounds__(256) void attn_staged_kernel(AttnArgs a) {
   }
 
   // write result (single split) or partials; lane holds hd 16t+4g4+i of query qrow
-  if (a.splits == 1) {
+  if (nsplit == 1) {
     if (qvalid) {
       const int tok = qrow / G, h = kvh * G + qrow % G;
       const float inv = lrun > 0.f ? 1.f / lrun : 0.f;
@@ -596,7 +610,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
       // span when its slots are shorter than the balanced plan's longest split by more
       // than the pipeline fill of a second segment (about three chunks, measured)
       sp = attn_span_plan(a, RBR);
-      const int S = a.n_seqs * a.row_blocks * a.splits;
+      const int S = a.slots;
       span = sp.ok && (a.span == 2 || (sp.total + S - 1) / S + 3 < attn_balanced_plan(a, RBR).q);
     }
   }
@@ -618,7 +632,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
   if (span) {
     unit = __builtin_ctzll(seg_units);
     seg_units &= seg_units - 1;
-    const int S = a.n_seqs * a.row_blocks * a.splits;
+    const int S = a.slots;
     const long b0 = (long)slot * sp.total / S, b1 = (long)(slot + 1) * sp.total / S;
     const int ustart = __builtin_amdgcn_readlane(sp.start, unit), un = __builtin_amdgcn_readlane(sp.n, unit);
     const int ufirst = __builtin_amdgcn_readlane(sp.first, unit);
@@ -1136,7 +1150,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
       o[t2][t][3] = fmaf(f1, v1.w, f0 * o[t2][t][3]);
     }
     const int qrow = row0 + rh * RH + rl;
-    if (a.splits == 1) {
+    if (nsplit == 1) {   // the unit's only split: no merge
       if (qrow < nrows) {
         const int tok = qrow / G, h = kvh * G + qrow % G;
         const float inv = L > 0.f ? 1.f / L : 0.f;
@@ -1188,6 +1202,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   if (rl >= RBR) return;
   const int2 us = attn_unit_slots(a, blockIdx.z);
   const int S = __builtin_amdgcn_readfirstlane(us.y);   // <= 64: one batch, or two
+  if (S == 1) return;                         // written by its split
   const int G = a.n_q_heads / a.n_kv_heads;
   const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
   const int r = rb * RBR + rl;
@@ -1262,18 +1277,37 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   for (int e = 0; e < PL; ++e) out[e] = Elem<T>::from_f32(num[e] * inv);
 }
 
-// One query tile per wave: 64-row blocks 8 waves with two LDS stages (64 KB at hd 128,
-// two workgroups per compute unit), or three (96 KB) where every split holds long key
+// One query tile per wave: 64-row blocks 8 waves with two LDS stages (64 KB at hd 128), or
+// three (96 KB) where every split holds long key
 // ranges: 8B batch-8 rounds 34.2 -> 32.6 us per layer (four stages 33.3), while the
 // short contexts of a 16-sequence serving batch ran 0.6 us slower with three; the kernel
 // that stages the q / k work's inputs keeps two (they take the third stage's room); 96-row
 // blocks 12 waves, three stages (96 KB; 15% faster than 4 waves of three tiles at the 14B
 // verify shape, where four stages measured no faster).  Results do not depend on the wave layout (the key-half
 // merge is written in explicit fused form).
+AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass) {
+  AttnSlots r{splits, n_units * splits, n_units * splits};
+  const int head = 256 / n_kv_heads;   // slots of one pass per KV head
+  if (!one_pass || splits < 2 || r.slots <= head) return r;
+  if (n_units < 2 || n_units > 64) {
+    r.splits = head / n_units > 1 ? head / n_units : 1;
+    r.slots = r.fit = n_units * r.splits;
+  } else {
+    r.fit = head > n_units ? head : n_units;
+    if (head / n_units >= 2) r.slots = r.fit;
+  }
+  return r;
+}
+
 template <typename T>
 hipError_t attention_partials(const AttnArgs& a, hipStream_t s) {
   if (a.blocks && (a.splits != 1 || a.qkv || a.n_blocks < 1)) return hipErrorInvalidValue;
-  dim3 grid(a.splits, a.n_kv_heads, a.blocks ? a.n_blocks : a.n_seqs * a.row_blocks);
+  const int units = a.n_seqs * a.row_blocks;
+  // a balanced launch of fewer slots than units * splits: one row of slots per head
+  const bool cut = !a.blocks && a.slots != units * a.splits;
+  if (cut && (a.splits < 2 || units < 2 || units > 64 || a.slots < units || a.slots > units * a.splits))
+    return hipErrorInvalidValue;
+  const dim3 grid(cut ? a.slots : a.splits, a.n_kv_heads, a.blocks ? a.n_blocks : cut ? 1 : units);
   // the fused q / k post-processing: bf16 kernels, blocks of at most 16 rows per sequence
   if (a.qkv && (sizeof(T) != 2 || a.rows_per_seq > 16 || a.nq)) return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 2) {
@@ -1297,8 +1331,7 @@ hipError_t attention_partials(const AttnArgs& a, hipStream_t s) {
       else return hipErrorInvalidValue;
     } else if (a.rb_rows == 64) {
       // a third stage where each split holds long key ranges (16 or more chunks at the
-      // longest context, one row block per sequence); otherwise two stages keep two
-      // workgroups per compute unit
+      // longest context, one row block per sequence)
       const bool deep = a.row_blocks == 1 && a.max_pages / 4 >= 16 * a.splits;
       if (a.head_dim == 128 && f) RT_LAUNCH((attn_bf16_kernel<128, 2, 1, 8, true>), grid, dim3(512), 0, s, a);
       else if (a.head_dim == 128 && deep) RT_LAUNCH((attn_bf16_kernel<128, 3, 1, 8, false>), grid, dim3(512), 0, s, a);
@@ -1334,6 +1367,7 @@ __global__ __launch_bounds__(256) void attn_merge16_kernel(AttnArgs a) {
   if (rl >= RBR) return;                      // whole rows leave together
   const int2 us = attn_unit_slots(a, blockIdx.z);
   const int S = us.y;                         // <= 64
+  if (S == 1) return;                         // written by its split
   const int G = a.n_q_heads / a.n_kv_heads;
   const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
   const int r = rb * RBR + rl;

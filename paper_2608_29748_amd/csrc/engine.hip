@@ -210,6 +210,10 @@ struct EngineBase {
   int debug_write(int id, int seq, const void* src, size_t bytes);
 };
 
+// Handles whose attention keeps to one pass of the chip (attn_slots): the rounds of up to 64
+// rows that this was measured on
+static bool attn_one_pass(const Plan& p) { return p.esz == 2 && p.R <= 64; }
+
 template <typename T, typename K>
 struct Engine : EngineBase {
   const char* tlayer(int l) const { return ws + p.t_layers + (size_t)l * p.layer_bytes; }
@@ -399,7 +403,8 @@ struct Engine : EngineBase {
     a.q = at<T>(q.qbuf); a.kcache = c.kc; a.vcache = c.vc; a.page_table = c.pt; a.max_pages = q.pages_per_seq;
     a.pos0 = c.pos0; a.nq = c.nq; a.seq_stride = c.stride; a.rows_per_seq = c.rows_per_seq;
     a.n_seqs = c.n_seqs; a.causal = c.causal; a.n_q_heads = q.Hq; a.n_kv_heads = q.Hkv; a.head_dim = q.hd;
-    a.splits = c.splits; a.row_blocks = c.rb; a.rb_rows = c.rb_rows;
+    const AttnSlots sl = attn_slots(c.n_seqs * c.rb, q.Hkv, c.splits, attn_one_pass(q));
+    a.splits = sl.splits; a.slots = sl.slots; a.fit = sl.fit; a.row_blocks = c.rb; a.rb_rows = c.rb_rows;
     a.blocks = c.blocks; a.n_blocks = c.n_blocks;
     // batches whose attention never takes the q / k work (so the fused and separate forms,
     // compared by a test hook, share one plan) may span unit boundaries
@@ -1607,6 +1612,22 @@ int rt_destroy(rt_model* m) {
   delete m->e;
   delete m;
   return RT_OK;
+}
+
+int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n_seqs, int32_t arg) {
+  Plan p;
+  const int st = make_plan(cfg, &p);
+  if (st) return st;
+  if (n_seqs < 1 || n_seqs > p.bmax) return fail(RT_ERR_CAPACITY, "n_seqs %d outside [1, %d]", n_seqs, p.bmax);
+  switch (choice) {
+    case RT_C_ATTN_SLOTS: {
+      if (arg != 1 && arg != p.bk) return fail(RT_ERR_INVALID, "rows per sequence must be 1 or the block size");
+      const bool step = arg == 1;
+      return attn_slots(n_seqs * (step ? p.ar_rb : p.attn_rb), p.Hkv, step ? p.ar_splits : p.attn_splits,
+                        attn_one_pass(p)).slots;
+    }
+    default: return fail(RT_ERR_INVALID, "unknown choice %d", choice);
+  }
 }
 
 const char* rt_last_error(void) { return rt::last_error(); }

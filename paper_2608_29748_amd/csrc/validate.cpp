@@ -125,12 +125,11 @@ int make_plan(const rt_config* c, Plan* p) {
   q.attn_rows = (c->dtype == RT_BF16 && q.bk * q.G > 64 && q.bk * q.G <= 96) ? 96 : 64;
   q.attn_rb = (q.bk * q.G + q.attn_rows - 1) / q.attn_rows;
   // key splits: about one workgroup per compute unit, at most 64 (one per lane of the
-  // merge), and at least two 64-key chunks per split at the longest sequence
+  // merge), and at least two 64-key chunks per split at the longest sequence; a launch may
+  // take fewer workgroups (attn_slots)
   auto key_splits = [&](int row_blocks) {
     const int base = q.bmax * q.Hkv * row_blocks;
-    // (the bf16 kernel of rounds of at most 64 rows fills a compute unit's LDS: a split
-    // too many for 256 units, as 11 x 24 at three sequences, would run after the others)
-    int sp = q.esz == 2 && q.R <= 64 ? 256 / base : (256 + base - 1) / base;
+    int sp = (256 + base - 1) / base;
     const int maxsp = ((q.T + 63) / 64) / 2;
     if (sp > maxsp) sp = maxsp;
     if (sp > 64) sp = 64;

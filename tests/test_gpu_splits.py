@@ -1,0 +1,41 @@
+"""Rounds of ragged batches whose attention shares fewer workgroups than whole splits per
+sequence, uses more of them than one pass of the chip holds, or writes one-split sequences
+without a merge."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from oracle import OracleModel, OracleRunner
+from paper_2608_29748_amd import binding as B
+from workloads import get, make_weights
+
+from gpu_parity import engine_for, log, run_teacher_forced
+from test_gpu_prefill import check_first
+
+pytestmark = pytest.mark.gpu
+
+
+# one long context among short ones: 32 of 40 slots hold it at 20 sequences, 62 are shared out
+# at 31 (32 would leave two for it); 25 slots of three sequences, 3 x 9 in whole splits
+@pytest.mark.parametrize("batch,block,kv_heads,head_dim,slots", [
+    (20, 3, 8, 128, 40), (31, 2, 8, 128, 62), (3, 16, 10, 128, 25), (20, 3, 8, 64, 40), (31, 2, 8, 64, 62)])
+def test_ragged_rounds_with_shared_slots_match_oracle(batch, block, kv_heads, head_dim, slots):
+    lens = [1150] + [5 + 3 * i for i in range(batch - 1)]
+    wl = get("mini-bf16", norm_init="perturbed", batch=batch, block_size=block, prompt_len=(5, 1150), new_tokens=30)
+    wl = wl.with_(target=replace(wl.target, n_layers=2, n_q_heads=2 * kv_heads, n_kv_heads=kv_heads,
+                                 head_dim=head_dim), cond_layers=(0, 1), draft_layers=1)
+    W = make_weights(wl)
+    rng = np.random.default_rng(9)
+    prompts = [rng.integers(0, wl.target.vocab // 2, size=n).astype(np.int32) for n in lens]
+    eng = engine_for(wl, W)
+    assert B.rt_debug_choice(eng.cfg, B.RT_C_ATTN_SLOTS, batch, block) == slots
+    R = OracleRunner(OracleModel(wl, W))
+    first = eng.prefill(prompts, wl.new_tokens)
+    states = [R.prefill(p, wl.new_tokens) for p in prompts]
+    check_first(first, R, prompts, states, 2e-2)
+    for f, st in zip(first, states):   # (at a near-tie both go on from the GPU's token)
+        st.anchor, st.generated = int(f), [int(f)]
+    rep = run_teacher_forced(eng, R, wl, states, 3, 2e-2, stages={})
+    log(f"[{batch} x {block}, {kv_heads} KV heads] rounds max err {rep.max_err}")
+    eng.close()
