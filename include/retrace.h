@@ -338,8 +338,9 @@ int rt_debug_write(rt_model* m, int32_t tensor_id, int32_t seq, const void* host
  * no GPU, so that tests can check that a size reaches the form it is meant for.  Returns a
  * negative RT_ERR_* code for an invalid argument. */
 enum {
-  RT_C_ATTN_SLOTS = 0      /* workgroups per KV head of the attention of a round (arg = block_size)
-                              or a target-only step (arg = 1) */
+  /* arg = rows per sequence: block_size (a round) or 1 (a target-only step) */
+  RT_C_ATTN_SLOTS = 0,     /* workgroups per KV head of the attention */
+  RT_C_PAGE_POST = 1       /* 1: q|k|v post-processing by KV page, 0: by row (where attention does not do it) */
 };
 int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n_seqs, int32_t arg);
 

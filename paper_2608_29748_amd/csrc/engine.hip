@@ -214,6 +214,16 @@ struct EngineBase {
 // rows that this was measured on
 static bool attn_one_pass(const Plan& p) { return p.esz == 2 && p.R <= 64; }
 
+// Rounds and steps that post-process q|k|v by KV page (a workgroup per page and head, sixteen
+// lanes a row) instead of one wave per row and head.  Enough rows to fill the chip, and enough
+// of a page's sixteen row places in use; us a launch, by row and by page: 4B widths, 1 row a
+// sequence 96 rows 6.6 and 14.4, 256 rows 11.8 and 30.3; 2 rows 256 11.6 and 18.1; 4 rows 512
+// 13.7 and 15.8; 5 rows 250 10.8 and 10.4; 8 rows 512 13.6 and 11.2; 16 rows 96 5.9 and 5.2,
+// 512 13.4 and 9.6.  fp32 (1024 wide): 16 rows 96 4.8 and 5.3, 256 6.0 and 5.5.
+static bool page_post(const Plan& p, int rows, int rows_per_seq) {
+  return rows_per_seq >= 5 && rows >= (p.esz == 2 ? 96 : 192);
+}
+
 template <typename T, typename K>
 struct Engine : EngineBase {
   const char* tlayer(int l) const { return ws + p.t_layers + (size_t)l * p.layer_bytes; }
@@ -292,8 +302,6 @@ struct Engine : EngineBase {
     return gemm_mid_store_slabs(g, false);
   }
 
-  // Rounds of at least this many rows post-process q|k|v by page (qkv_post_pages)
-  static constexpr int kPageRows = 96;
   struct LayerCtx {
     int M, rows_per_seq, n_seqs, stride, causal, splits, rb, rb_rows;
     const int32_t* pos0;
@@ -395,7 +403,8 @@ struct Engine : EngineBase {
       qp.rows_per_seq = c.rows_per_seq; qp.seq_stride = c.stride; qp.pos0 = c.pos0; qp.nrows = nullptr;
       prof_begin(RT_K_QKV_POST, (double)c.M * q.qkvN * (4 * qks + sizeof(T)), 0);
       HIPCHK(c.items ? qkv_post_pages<T>(qp, c.items, c.n_items, stream)
-             : c.M >= kPageRows ? qkv_post_pages<T>(qp, nullptr, c.n_seqs, stream) : qkv_post<T>(qp, stream));
+             : page_post(q, c.M, c.rows_per_seq) ? qkv_post_pages<T>(qp, nullptr, c.n_seqs, stream)
+                                                 : qkv_post<T>(qp, stream));
       prof_end();
       CHK(trace_item(c.trace, TI_Q, at<T>(q.qbuf)));
     }
@@ -541,7 +550,8 @@ struct Engine : EngineBase {
     qp.rows_per_seq = rows_per_seq; qp.seq_stride = stride; qp.pos0 = pos0; qp.nrows = nrows;
     prof_begin(RT_K_QKV_POST, (double)M * q.LD * 2 * q.kvN * (4 + sizeof(T)), 0);
     HIPCHK(items ? qkv_post_pages<T>(qp, items, n_items, stream)
-           : M >= kPageRows ? qkv_post_pages<T>(qp, nullptr, M / rows_per_seq, stream) : qkv_post<T>(qp, stream));
+           : page_post(q, M, rows_per_seq) ? qkv_post_pages<T>(qp, nullptr, M / rows_per_seq, stream)
+                                           : qkv_post<T>(qp, stream));
     prof_end();
     return RT_OK;
   }
@@ -1619,13 +1629,14 @@ int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n_seqs, int32_
   const int st = make_plan(cfg, &p);
   if (st) return st;
   if (n_seqs < 1 || n_seqs > p.bmax) return fail(RT_ERR_CAPACITY, "n_seqs %d outside [1, %d]", n_seqs, p.bmax);
+  if (arg != 1 && arg != p.bk) return fail(RT_ERR_INVALID, "rows per sequence must be 1 or the block size");
   switch (choice) {
     case RT_C_ATTN_SLOTS: {
-      if (arg != 1 && arg != p.bk) return fail(RT_ERR_INVALID, "rows per sequence must be 1 or the block size");
       const bool step = arg == 1;
       return attn_slots(n_seqs * (step ? p.ar_rb : p.attn_rb), p.Hkv, step ? p.ar_splits : p.attn_splits,
                         attn_one_pass(p)).slots;
     }
+    case RT_C_PAGE_POST: return page_post(p, n_seqs * arg, arg);
     default: return fail(RT_ERR_INVALID, "unknown choice %d", choice);
   }
 }

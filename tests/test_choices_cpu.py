@@ -40,3 +40,14 @@ def test_attention_slots(batch, block, head_dim, slots):
                              block) == units * -(-256 // (8 * units))
     one = cfg(max_batch=1, n_q_heads=24, n_kv_heads=24)
     assert B.rt_debug_choice(one, B.RT_C_ATTN_SLOTS, 1, 16) == 10
+
+
+# pages of five rows or more in use, and enough rows: 96 in bf16, 192 in fp32
+@pytest.mark.parametrize("dtype,batch,block,by_page", [
+    (B.RT_BF16, 6, 16, 1), (B.RT_BF16, 5, 16, 0), (B.RT_BF16, 20, 5, 1), (B.RT_BF16, 24, 4, 0),
+    (B.RT_BF16, 128, 2, 0), (B.RT_F32, 12, 16, 1), (B.RT_F32, 11, 16, 0), (B.RT_F32, 64, 4, 0)])
+def test_qkv_post_by_page(dtype, batch, block, by_page):
+    c = cfg(dtype=dtype, max_batch=256, block_size=block)
+    assert B.rt_debug_choice(c, B.RT_C_PAGE_POST, batch, block) == by_page
+    for n in (1, 96, 256):                                    # target-only steps: one row a page
+        assert B.rt_debug_choice(c, B.RT_C_PAGE_POST, n, 1) == 0

@@ -1,6 +1,6 @@
 """Rounds of ragged batches whose attention shares fewer workgroups than whole splits per
 sequence, uses more of them than one pass of the chip holds, or writes one-split sequences
-without a merge."""
+without a merge; and of batches on either side of the page-wise q|k|v post-processing."""
 from dataclasses import replace
 
 import numpy as np
@@ -14,6 +14,19 @@ from gpu_parity import engine_for, log, run_teacher_forced
 from test_gpu_prefill import check_first
 
 pytestmark = pytest.mark.gpu
+
+
+def teacher_forced(eng, wl, W, prompts):
+    tol = {"f32": 1e-4, "bf16": 2e-2}[wl.dtype]
+    R = OracleRunner(OracleModel(wl, W))
+    first = eng.prefill(prompts, wl.new_tokens)
+    states = [R.prefill(p, wl.new_tokens) for p in prompts]
+    check_first(first, R, prompts, states, tol)
+    for f, st in zip(first, states):   # (at a near-tie both go on from the GPU's token)
+        st.anchor, st.generated = int(f), [int(f)]
+    rep = run_teacher_forced(eng, R, wl, states, 3, tol, stages={})
+    log(f"[{wl.name} {wl.batch} x {wl.block_size}] rounds max err {rep.max_err}")
+    eng.close()
 
 
 # one long context among short ones: 32 of 40 slots hold it at 20 sequences, 62 are shared out
@@ -30,12 +43,17 @@ def test_ragged_rounds_with_shared_slots_match_oracle(batch, block, kv_heads, he
     prompts = [rng.integers(0, wl.target.vocab // 2, size=n).astype(np.int32) for n in lens]
     eng = engine_for(wl, W)
     assert B.rt_debug_choice(eng.cfg, B.RT_C_ATTN_SLOTS, batch, block) == slots
-    R = OracleRunner(OracleModel(wl, W))
-    first = eng.prefill(prompts, wl.new_tokens)
-    states = [R.prefill(p, wl.new_tokens) for p in prompts]
-    check_first(first, R, prompts, states, 2e-2)
-    for f, st in zip(first, states):   # (at a near-tie both go on from the GPU's token)
-        st.anchor, st.generated = int(f), [int(f)]
-    rep = run_teacher_forced(eng, R, wl, states, 3, 2e-2, stages={})
-    log(f"[{batch} x {block}, {kv_heads} KV heads] rounds max err {rep.max_err}")
-    eng.close()
+    teacher_forced(eng, wl, W, prompts)
+
+
+# by row: too few rows of a page in use, or too few rows; by page: 5 rows (pages crossed), 16
+@pytest.mark.parametrize("name,batch,block,by_page", [
+    ("mini-bf16", 50, 2, 0), ("mini-bf16", 20, 5, 1), ("tiny-f32", 11, 16, 0), ("tiny-f32", 12, 16, 1)])
+def test_rounds_by_row_and_by_page_match_oracle(name, batch, block, by_page):
+    wl = get(name, norm_init="perturbed", batch=batch, block_size=block, prompt_len=(5, 60), new_tokens=30)
+    W = make_weights(wl)
+    rng = np.random.default_rng(10)
+    prompts = [rng.integers(0, wl.target.vocab // 2, size=5 + i % 40).astype(np.int32) for i in range(batch)]
+    eng = engine_for(wl, W)
+    assert B.rt_debug_choice(eng.cfg, B.RT_C_PAGE_POST, batch, block) == by_page
+    teacher_forced(eng, wl, W, prompts)
