@@ -334,15 +334,16 @@ int rt_debug_read_rows(rt_model* m, int32_t tensor_id, int32_t seq, int32_t pos0
  * computed elsewhere). */
 int rt_debug_write(rt_model* m, int32_t tensor_id, int32_t seq, const void* host_src, size_t bytes);
 
-/* What the library would launch for n_seqs sequences of a configuration; needs no model and
- * no GPU, so that tests can check that a size reaches the form it is meant for.  Returns a
- * negative RT_ERR_* code for an invalid argument. */
+/* What the library would launch for a configuration; needs no model and no GPU, so that tests
+ * can check that a size reaches the form it is meant for.  Returns a negative RT_ERR_* code
+ * for an invalid argument. */
 enum {
-  /* arg = rows per sequence: block_size (a round) or 1 (a target-only step) */
+  /* n sequences of arg rows: block_size (a round) or 1 (a target-only step) */
   RT_C_ATTN_SLOTS = 0,     /* workgroups per KV head of the attention */
-  RT_C_PAGE_POST = 1       /* 1: q|k|v post-processing by KV page, 0: by row (where attention does not do it) */
+  RT_C_PAGE_POST = 1,      /* 1: q|k|v post-processing by KV page, 0: by row (where attention does not do it) */
+  RT_C_PROMPT_ROWS = 2     /* rows per pass of a prefill of n prompt tokens in all (arg unused) */
 };
-int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n_seqs, int32_t arg);
+int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n, int32_t arg);
 
 #ifdef __cplusplus
 }

@@ -40,7 +40,7 @@ RT_T_TRACE_TARGET_Q, RT_T_TRACE_TARGET_ATTN, RT_T_TRACE_TARGET_XMID, RT_T_TRACE_
 RT_K_KINDS = 12
 KERNEL_KIND_NAMES = ["gemm_qkv", "gemm_o", "gemm_gate_up", "gemm_down", "gemm_context", "gemm_cond",
                      "attention", "attn_merge", "rmsnorm", "qkv_post", "lm_head", "misc"]
-RT_C_ATTN_SLOTS, RT_C_PAGE_POST = range(2)
+RT_C_ATTN_SLOTS, RT_C_PAGE_POST, RT_C_PROMPT_ROWS = range(3)
 STAGE_NAMES = ["condition", "draft", "draft_lm_head", "verify", "verify_lm_head", "accept", "context_append"]
 RT_PROF_STAGES = 7
 
@@ -266,9 +266,9 @@ def rt_debug_write(h: int, tensor_id: int, seq: int, data: bytes) -> None:
     _check(_lib.rt_debug_write(C.c_void_p(h), tensor_id, seq, buf, len(data)))
 
 
-def rt_debug_choice(cfg: rt_config, choice: int, n_seqs: int, arg: int) -> int:
-    """What the library would launch (RT_C_*) for n_seqs sequences; needs no GPU."""
-    v = _lib.rt_debug_choice(C.byref(cfg), choice, n_seqs, arg)
+def rt_debug_choice(cfg: rt_config, choice: int, n: int, arg: int = 0) -> int:
+    """What the library would launch (RT_C_*); needs no GPU."""
+    v = _lib.rt_debug_choice(C.byref(cfg), choice, n, arg)
     if v < 0:
         _check(v)
     return v

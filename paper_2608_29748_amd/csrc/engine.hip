@@ -214,6 +214,14 @@ struct EngineBase {
 // rows that this was measured on
 static bool attn_one_pass(const Plan& p) { return p.esz == 2 && p.R <= 64; }
 
+// Rows of a pass over `total` prompt rows: passes of about equal rows.  33..64 rows of fp32 run
+// as two passes on the skinny kernels: the 128-row tiles of more rows leave the chip idle (two
+// prompts of 30 tokens, 1024 wide, 4 layers: 1194 us in one pass, 634 in two).
+static int prompt_pass_rows(const Plan& p, int total) {
+  if (p.esz == 4 && total > 32 && total <= 64) return 32;
+  const int n_pass = (total + p.PF - 1) / p.PF;
+  return (int)rup((size_t)(total + n_pass - 1) / n_pass, 256);
+}
 // Rounds and steps that post-process q|k|v by KV page (a workgroup per page and head, sixteen
 // lanes a row) instead of one wave per row and head.  Enough rows to fill the chip, and enough
 // of a page's sixteen row places in use; us a launch, by row and by page: 4B widths, 1 row a
@@ -648,8 +656,7 @@ struct Engine : EngineBase {
     t.assign(ids, ids + total);
     out->off = t.size();
     t.insert(t.end(), off.begin(), off.end());
-    const int n_pass = (total + q.PF - 1) / q.PF;
-    const int per = (int)rup((size_t)(total + n_pass - 1) / n_pass, 256);   // passes of about equal rows
+    const int per = prompt_pass_rows(q, total);
     const int rbr = sizeof(T) == 2 ? kAttnRowsPrompt : kAttnRows;
     struct Blk { int s, row, n, pos, rb, keys; };
     std::vector<Blk> blk;
@@ -1624,19 +1631,23 @@ int rt_destroy(rt_model* m) {
   return RT_OK;
 }
 
-int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n_seqs, int32_t arg) {
+int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n, int32_t arg) {
   Plan p;
   const int st = make_plan(cfg, &p);
   if (st) return st;
-  if (n_seqs < 1 || n_seqs > p.bmax) return fail(RT_ERR_CAPACITY, "n_seqs %d outside [1, %d]", n_seqs, p.bmax);
+  if (choice == RT_C_PROMPT_ROWS) {
+    if (n < 1 || n > p.bmax * (long long)p.T) return fail(RT_ERR_CAPACITY, "%d prompt rows", n);
+    return prompt_pass_rows(p, n);
+  }
+  if (n < 1 || n > p.bmax) return fail(RT_ERR_CAPACITY, "%d sequences outside [1, %d]", n, p.bmax);
   if (arg != 1 && arg != p.bk) return fail(RT_ERR_INVALID, "rows per sequence must be 1 or the block size");
   switch (choice) {
     case RT_C_ATTN_SLOTS: {
       const bool step = arg == 1;
-      return attn_slots(n_seqs * (step ? p.ar_rb : p.attn_rb), p.Hkv, step ? p.ar_splits : p.attn_splits,
+      return attn_slots(n * (step ? p.ar_rb : p.attn_rb), p.Hkv, step ? p.ar_splits : p.attn_splits,
                         attn_one_pass(p)).slots;
     }
-    case RT_C_PAGE_POST: return page_post(p, n_seqs * arg, arg);
+    case RT_C_PAGE_POST: return page_post(p, n * arg, arg);
     default: return fail(RT_ERR_INVALID, "unknown choice %d", choice);
   }
 }

@@ -51,3 +51,14 @@ def test_qkv_post_by_page(dtype, batch, block, by_page):
     assert B.rt_debug_choice(c, B.RT_C_PAGE_POST, batch, block) == by_page
     for n in (1, 96, 256):                                    # target-only steps: one row a page
         assert B.rt_debug_choice(c, B.RT_C_PAGE_POST, n, 1) == 0
+
+
+@pytest.mark.parametrize("dtype,total,rows", [
+    (B.RT_F32, 32, 256), (B.RT_F32, 33, 32), (B.RT_F32, 60, 32), (B.RT_F32, 64, 32), (B.RT_F32, 65, 256),
+    (B.RT_BF16, 60, 256), (B.RT_BF16, 4096, 4096), (B.RT_BF16, 4097, 2304), (B.RT_BF16, 9000, 3072)])
+def test_prompt_rows_per_pass(dtype, total, rows):
+    c = cfg(dtype=dtype, max_batch=4)
+    assert B.rt_debug_choice(c, B.RT_C_PROMPT_ROWS, total) == rows
+    for bad in (0, 4 * 8400 + 1):
+        with pytest.raises(B.RetraceError):
+            B.rt_debug_choice(c, B.RT_C_PROMPT_ROWS, bad)

@@ -1,6 +1,7 @@
 """Rounds of ragged batches whose attention shares fewer workgroups than whole splits per
 sequence, uses more of them than one pass of the chip holds, or writes one-split sequences
-without a merge; and of batches on either side of the page-wise q|k|v post-processing."""
+without a merge; of batches on either side of the page-wise q|k|v post-processing; and fp32
+prompts in two passes of at most 32 rows."""
 from dataclasses import replace
 
 import numpy as np
@@ -10,18 +11,20 @@ from oracle import OracleModel, OracleRunner
 from paper_2608_29748_amd import binding as B
 from workloads import get, make_weights
 
-from gpu_parity import engine_for, log, run_teacher_forced
+from gpu_parity import compare_prefill, engine_for, log, run_teacher_forced
 from test_gpu_prefill import check_first
 
 pytestmark = pytest.mark.gpu
 
 
-def teacher_forced(eng, wl, W, prompts):
+def teacher_forced(eng, wl, W, prompts, prefill=False):
     tol = {"f32": 1e-4, "bf16": 2e-2}[wl.dtype]
     R = OracleRunner(OracleModel(wl, W))
     first = eng.prefill(prompts, wl.new_tokens)
     states = [R.prefill(p, wl.new_tokens) for p in prompts]
     check_first(first, R, prompts, states, tol)
+    if prefill:
+        compare_prefill(eng, R, wl, prompts, states, tol)
     for f, st in zip(first, states):   # (at a near-tie both go on from the GPU's token)
         st.anchor, st.generated = int(f), [int(f)]
     rep = run_teacher_forced(eng, R, wl, states, 3, tol, stages={})
@@ -57,3 +60,15 @@ def test_rounds_by_row_and_by_page_match_oracle(name, batch, block, by_page):
     eng = engine_for(wl, W)
     assert B.rt_debug_choice(eng.cfg, B.RT_C_PAGE_POST, batch, block) == by_page
     teacher_forced(eng, wl, W, prompts)
+
+
+# passes cut inside a sequence and a page; on a sequence's end; one prompt of both passes
+@pytest.mark.parametrize("lens", [(30, 30), (20, 12, 13), (33,), (64,), (1, 40, 2)])
+def test_fp32_prompts_of_two_small_passes_match_oracle(lens):
+    wl = get("tiny-f32", norm_init="perturbed", batch=len(lens), prompt_len=(min(lens), max(lens)), new_tokens=30)
+    W = make_weights(wl)
+    rng = np.random.default_rng(11)
+    prompts = [rng.integers(0, wl.target.vocab // 2, size=n).astype(np.int32) for n in lens]
+    eng = engine_for(wl, W)
+    assert B.rt_debug_choice(eng.cfg, B.RT_C_PROMPT_ROWS, sum(lens)) == 32
+    teacher_forced(eng, wl, W, prompts, prefill=True)
