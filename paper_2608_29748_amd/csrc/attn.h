@@ -10,11 +10,10 @@ struct AttnArgs {
   const void* vcache;            // this layer: V pages [page][kv head][hd][token]
   const int32_t* page_table; int max_pages;
   const int32_t* pos0;           // [seq * seq_stride] position of query token 0
-  const int32_t* nq;             // [seq * seq_stride] valid query tokens (null: rows_per_seq)
   int seq_stride;
   int rows_per_seq;
   int n_seqs;
-  int causal;                    // 1: key position <= query position; 0: every key below pos0+nq
+  int causal;                    // 1: key position <= query position; 0: every key below pos0 + rows_per_seq
   int n_q_heads, n_kv_heads, head_dim;
   int splits;                    // key-range splits per (seq, kv head, row block)
   int slots, fit;                // workgroups per KV head, and those of one pass of the chip: see attn_slots
@@ -22,7 +21,7 @@ struct AttnArgs {
   int rb_rows;                   // rows per block: 64, or 96 (bf16) when a sequence has 65..96 rows
   // Prompt passes (one key split): grid.z entry z works on the block
   // blocks[z] = {sequence, activation row of its segment's token 0, tokens of the segment,
-  // position of token 0, row block within the segment, 0, 0, 0}; n_blocks of them.  pos0, nq,
+  // position of token 0, row block within the segment, 0, 0, 0}; n_blocks of them.  pos0,
   // rows_per_seq, n_seqs and row_blocks are then unused.
   const int32_t* blocks; int n_blocks;
   // split partials: per (split, row) the running max and sum (fp32 mlpart) and the
@@ -67,13 +66,10 @@ constexpr int kAttnBlockInts = 8;      // int32 per entry of AttnArgs::blocks
 struct AttnSlots { int splits, slots, fit; };
 AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass);
 
-// attention = attention_partials (per key split) then attention_merge (splits > 1).
-template <typename T>
-hipError_t attention(const AttnArgs& a, hipStream_t s);
+// Attention: attention_partials (per key split), then attention_merge (splits > 1).
 template <typename T>
 hipError_t attention_partials(const AttnArgs& a, hipStream_t s);
 template <typename T>
 hipError_t attention_merge(const AttnArgs& a, hipStream_t s);
-size_t attn_partial_floats(int n_seqs, int n_kv_heads, int row_blocks, int splits, int head_dim, int rb_rows);
 
 }  // namespace rt

@@ -57,10 +57,6 @@ template <> struct PartOf<float> {
   }
 };
 
-size_t attn_partial_floats(int n_seqs, int n_kv_heads, int row_blocks, int splits, int head_dim, int rb_rows) {
-  return (size_t)n_kv_heads * ((size_t)n_seqs * row_blocks * (splits + 1) - 1) * rb_rows * head_dim;
-}
-
 // wave-wide integer reductions and scan of the ROCm device library (DPP based)
 extern "C" __device__ int __ockl_wfred_add_i32(int);
 extern "C" __device__ int __ockl_wfred_max_i32(int);
@@ -86,8 +82,7 @@ __device__ __forceinline__ bool attn_balanced(const AttnArgs& a) {
 __device__ __forceinline__ int attn_unit_chunks(const AttnArgs& a, int u, int rbr) {
   const int s = u / a.row_blocks, rb = u % a.row_blocks;
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
-  const int nrows = nq * G, row0 = rb * rbr;
+  const int nq = a.rows_per_seq, nrows = nq * G, row0 = rb * rbr;
   if (row0 >= nrows) return 0;
   const int P = a.pos0[s * a.seq_stride];
   const int last_tok = min(nrows, row0 + rbr) - 1;
@@ -138,8 +133,7 @@ __device__ __forceinline__ UnitInfo attn_unit(const AttnArgs& a, int unit) {
     return UnitInfo{b[0], b[4], b[2], b[3], b[1]};
   }
   const int s = unit / a.row_blocks;
-  return UnitInfo{s, unit % a.row_blocks, a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq, a.pos0[s * a.seq_stride],
-                  s * a.rows_per_seq};
+  return UnitInfo{s, unit % a.row_blocks, a.rows_per_seq, a.pos0[s * a.seq_stride], s * a.rows_per_seq};
 }
 // Work of the workgroup at (blockIdx.x, blockIdx.z): unit, split index within the unit
 // and the unit's split count; false for a slot the balanced plan leaves idle.
@@ -1204,9 +1198,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int S = __builtin_amdgcn_readfirstlane(us.y);   // <= 64: one batch, or two
   if (S == 1) return;                         // written by its split
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
   const int r = rb * RBR + rl;
-  if (r >= nq * G) return;
+  if (r >= a.rows_per_seq * G) return;
   const int tok = r / G, h = kvh * G + r % G;
   T* out = (T*)a.out + pa_index(s * a.rows_per_seq + tok, h * HD + c * PL, a.ldo);   // PL elements of one 8-element run
   if (S <= 0) {   // no split holds keys of this unit (not produced by the plans)
@@ -1309,7 +1302,7 @@ hipError_t attention_partials(const AttnArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   const dim3 grid(cut ? a.slots : a.splits, a.n_kv_heads, a.blocks ? a.n_blocks : cut ? 1 : units);
   // the fused q / k post-processing: bf16 kernels, blocks of at most 16 rows per sequence
-  if (a.qkv && (sizeof(T) != 2 || a.rows_per_seq > 16 || a.nq)) return hipErrorInvalidValue;
+  if (a.qkv && (sizeof(T) != 2 || a.rows_per_seq > 16)) return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 2) {
     const bool f = a.qkv != nullptr;
     if (a.blocks) {
@@ -1369,9 +1362,8 @@ __global__ __launch_bounds__(256) void attn_merge16_kernel(AttnArgs a) {
   const int S = us.y;                         // <= 64
   if (S == 1) return;                         // written by its split
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int nq = a.nq ? a.nq[s * a.seq_stride] : a.rows_per_seq;
   const int r = rb * RBR + rl;
-  if (r >= nq * G) return;
+  if (r >= a.rows_per_seq * G) return;
   if (S <= 0) {   // no split holds keys of this unit (not produced by the plans)
     const int tok = r / G, h = kvh * G + r % G;
 #pragma unroll
@@ -1454,13 +1446,6 @@ hipError_t attention_merge(const AttnArgs& a, hipStream_t s) {
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
-template <typename T>
-hipError_t attention(const AttnArgs& a, hipStream_t s) {
-  hipError_t e = attention_partials<T>(a, s);
-  return e != hipSuccess ? e : attention_merge<T>(a, s);
-}
-template hipError_t attention<bf16_t>(const AttnArgs&, hipStream_t);
-template hipError_t attention<float>(const AttnArgs&, hipStream_t);
 template hipError_t attention_partials<bf16_t>(const AttnArgs&, hipStream_t);
 template hipError_t attention_partials<float>(const AttnArgs&, hipStream_t);
 template hipError_t attention_merge<bf16_t>(const AttnArgs&, hipStream_t);

@@ -313,7 +313,6 @@ struct Engine : EngineBase {
   struct LayerCtx {
     int M, rows_per_seq, n_seqs, stride, causal, splits, rb, rb_rows;
     const int32_t* pos0;
-    const int32_t* nq;
     const int32_t* pt;
     T* kc;
     T* vc;
@@ -323,7 +322,7 @@ struct Engine : EngineBase {
     int defer;                   // o / down (<= 32 rows): k-slab partials, added by the next norm
     int trace = -1;              // layer-trace record of this layer (-1: none)
     // prompt pass: its attention blocks and page items (then rows_per_seq, n_seqs, stride,
-    // rb, pos0 and nq are unused)
+    // rb and pos0 are unused)
     const int32_t* blocks = nullptr;
     int n_blocks = 0;
     const int32_t* items = nullptr;
@@ -418,7 +417,7 @@ struct Engine : EngineBase {
     }
     AttnArgs a{};
     a.q = at<T>(q.qbuf); a.kcache = c.kc; a.vcache = c.vc; a.page_table = c.pt; a.max_pages = q.pages_per_seq;
-    a.pos0 = c.pos0; a.nq = c.nq; a.seq_stride = c.stride; a.rows_per_seq = c.rows_per_seq;
+    a.pos0 = c.pos0; a.seq_stride = c.stride; a.rows_per_seq = c.rows_per_seq;
     a.n_seqs = c.n_seqs; a.causal = c.causal; a.n_q_heads = q.Hq; a.n_kv_heads = q.Hkv; a.head_dim = q.hd;
     const AttnSlots sl = attn_slots(c.n_seqs * c.rb, q.Hkv, c.splits, attn_one_pass(q));
     a.splits = sl.splits; a.slots = sl.slots; a.fit = sl.fit; a.row_blocks = c.rb; a.rb_rows = c.rb_rows;
@@ -779,7 +778,7 @@ struct Engine : EngineBase {
     float* last = at<float>(q.fcout);
     for (int l = 0; l < q.L; ++l) {
       const int slot = cond_slot(l);
-      LayerCtx c{n, n, 1, 0, 1, 1, 1, rbr, nullptr, nullptr, ptab,
+      LayerCtx c{n, n, 1, 0, 1, 1, 1, rbr, nullptr, ptab,
                  at<T>(q.kc) + (size_t)l * q.cache_layer_elems, at<T>(q.vc) + (size_t)l * q.cache_layer_elems,
                  slot >= 0 ? at<T>(q.g) : nullptr, slot * q.d, nullptr, l + 1 < q.L};
       c.blocks = tab + ps.blocks; c.n_blocks = ps.n_blocks;
@@ -865,7 +864,7 @@ struct Engine : EngineBase {
     stage(1);
     // (2) drafter: B+1 rows at P..P+B over its context cache (no causal mask in the block)
     for (int l = 0; l < q.LD; ++l) {
-      LayerCtx c{R, q.bk, n_seqs, kStateFields, 0, q.attn_splits, q.attn_rb, q.attn_rows, st + ST_SEQ_LEN, nullptr, pt,
+      LayerCtx c{R, q.bk, n_seqs, kStateFields, 0, q.attn_splits, q.attn_rb, q.attn_rows, st + ST_SEQ_LEN, pt,
                  at<T>(q.dkc) + (size_t)l * q.cache_layer_elems, at<T>(q.dvc) + (size_t)l * q.cache_layer_elems,
                  nullptr, 0, prof_ctx.data(), 1};
       c.trace = l;
@@ -889,7 +888,7 @@ struct Engine : EngineBase {
     prof_end();
     for (int l = 0; l < q.L; ++l) {
       const int slot = cond_slot(l);
-      LayerCtx c{R, q.bk, n_seqs, kStateFields, 1, q.attn_splits, q.attn_rb, q.attn_rows, st + ST_SEQ_LEN, nullptr, pt,
+      LayerCtx c{R, q.bk, n_seqs, kStateFields, 1, q.attn_splits, q.attn_rb, q.attn_rows, st + ST_SEQ_LEN, pt,
                  at<T>(q.kc) + (size_t)l * q.cache_layer_elems, at<T>(q.vc) + (size_t)l * q.cache_layer_elems,
                  slot >= 0 ? at<T>(q.g) : nullptr, slot * q.d, prof_ctx.data(), 1};
       c.trace = q.LD + l;
@@ -942,7 +941,7 @@ struct Engine : EngineBase {
                       q.d, stream);
     prof_end();
     for (int l = 0; l < q.L; ++l) {
-      LayerCtx c{M, 1, n_seqs, kStateFields, 1, q.ar_splits, q.ar_rb, kAttnRows, st + ST_SEQ_LEN, nullptr, pt,
+      LayerCtx c{M, 1, n_seqs, kStateFields, 1, q.ar_splits, q.ar_rb, kAttnRows, st + ST_SEQ_LEN, pt,
                  at<T>(q.kc) + (size_t)l * q.cache_layer_elems, at<T>(q.vc) + (size_t)l * q.cache_layer_elems,
                  nullptr, 0, prof_ctx.data(), 1};
       CHK(layer(tlayer(l), c));
@@ -955,7 +954,7 @@ struct Engine : EngineBase {
                 at<int32_t>(q.stok)));
     prof_begin(RT_K_MISC, (double)M * 16, 0);
     ar_commit(st, at<uint64_t>(q.tkeys), smp ? at<int32_t>(q.stok) : nullptr, n_seqs, at<int32_t>(q.ar_tok),
-              kArMaxSteps, at<int32_t>(q.pf_ints) + 8, stream);
+              kArMaxSteps, at<int32_t>(q.ar_step), stream);
     prof_end();
     HIPCHK(hipGetLastError());
     return RT_OK;
@@ -973,7 +972,7 @@ int EngineBase::ar_steps(int n, int32_t* tokens, int32_t* n_gen) {
   if (n < 1 || n > kArMaxSteps) return fail(RT_ERR_INVALID, "n_steps must be in [1, %d]", kArMaxSteps);
   const Plan& q = p;
   ar_mode = true;
-  set_ints(at<int32_t>(q.pf_ints) + 8, 1, 0, 0, 0, 0, stream);   // step counter (outside the graph)
+  set_ints(at<int32_t>(q.ar_step), 1, 0, 0, 0, 0, stream);   // step counter (outside the graph)
   HIPCHK(hipGetLastError());
   if (flags & 2) {
     for (int i = 0; i < n; ++i) CHK(run_ar_step());

@@ -921,7 +921,6 @@ int lmhead_parts(int M, int N, int Kp, int elem_bytes) {
   const int need = (N / kTileN + kLmWaves - 1) / kLmWaves;
   return grid < need ? grid : need;
 }
-int lmhead_max_parts(int N) { return lmhead_grid(N) > kLmGrid ? lmhead_grid(N) : kLmGrid; }
 
 template <typename T>
 hipError_t lm_head(const LmHeadArgs& a, hipStream_t s) {

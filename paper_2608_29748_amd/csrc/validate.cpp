@@ -185,7 +185,7 @@ int make_plan(const rt_config* c, Plan* p) {
   q.page_table = take((size_t)q.n_pages * 4);
   q.rope = take((size_t)q.T * (q.hd / 2) * 2 * 4);
   q.state = take((size_t)q.bmax * kStateSlots * 4);
-  q.pf_ints = take(16 * 4);
+  q.ar_step = take(4);
   q.first_tok = take((size_t)q.bmax * 4);
   q.counters = take((size_t)kMaxTiles * 4);
   q.partial = take(kPartialFloats * 4);
