@@ -240,9 +240,11 @@ int make_plan(const rt_config* c, Plan* p) {
   q.out_a = take((size_t)q.bmax * 4);
   {
     // tokens and offsets; per (sequence, pass) segment at most rows / 64 + 1 attention blocks
-    // and rows / 16 + 2 page items; per sequence one more block (its last rows)
-    const size_t tok = (size_t)q.bmax * q.T, seg = (size_t)q.bmax + tok / q.PF + 2;
-    q.pf_tab_ints = tok + 9 * (size_t)q.bmax + 1 + 8 * (tok * q.G / 64 + seg) + 4 * (tok / 16 + 2 * seg) + 64;
+    // and rows / 16 + 2 page items; per sequence once more the blocks that its last token's G
+    // rows meet; up to 3 ints of padding a pass
+    const size_t tok = (size_t)q.bmax * q.T, pass = tok / q.PF + 2, seg = (size_t)q.bmax + pass;
+    const size_t ends = (size_t)q.bmax * ((q.G + 62) / 64 + 1);
+    q.pf_tab_ints = tok + q.bmax + 1 + 8 * (tok * q.G / 64 + seg + ends) + 4 * (tok / 16 + 2 * seg) + 3 * pass;
     q.pf_tab = take(q.pf_tab_ints * 4);
   }
   q.ar_tok = take((size_t)q.bmax * kArMaxSteps * 4);
