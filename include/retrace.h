@@ -140,7 +140,11 @@ int rt_init_models(const rt_config* cfg, const void* const* weights, int32_t n_w
  * KV cache, and returns each sequence's first generated token (greedy) in
  * first_tokens[n_seqs] (host).  gen_budget counts new tokens per sequence, the
  * first one included; prompt_len + gen_budget + block_size must not exceed
- * max_seq_len.  Resets all round state (nothing is carried into round 1). */
+ * max_seq_len.  Resets all round state (nothing is carried into round 1).
+ * The prompts of one call share passes of up to 4096 rows, and tile widths and reduction
+ * splits follow a pass's row count.  In bf16 and fp32 alike, a prompt's cached keys and values
+ * and its first token's logits may therefore differ in the last rounding from those of the same
+ * prompt in another batch; the same call repeated gives the same bits. */
 int rt_prefill(rt_model* m, int32_t n_seqs, const int32_t* prompt_lens, const int32_t* prompt_ids,
                int32_t gen_budget, int32_t* first_tokens);
 
@@ -341,7 +345,10 @@ enum {
   /* n sequences of arg rows: block_size (a round) or 1 (a target-only step) */
   RT_C_ATTN_SLOTS = 0,     /* workgroups per KV head of the attention */
   RT_C_PAGE_POST = 1,      /* 1: q|k|v post-processing by KV page, 0: by row (where attention does not do it) */
-  RT_C_PROMPT_ROWS = 2     /* rows per pass of a prefill of n prompt tokens in all (arg unused) */
+  RT_C_PROMPT_ROWS = 2,    /* rows per pass of a prefill of n prompt tokens in all (arg unused) */
+  RT_C_GEMM_COLS = 3       /* columns per workgroup of the target GEMM arg (RT_K_GEMM_QKV .. _DOWN, RT_K_LM_HEAD)
+                              over n rows of a prompt pass (LM head: a round) on the mid-size kernel; 0 where
+                              another kernel runs */
 };
 int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n, int32_t arg);
 

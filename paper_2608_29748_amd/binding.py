@@ -40,7 +40,7 @@ RT_T_TRACE_TARGET_Q, RT_T_TRACE_TARGET_ATTN, RT_T_TRACE_TARGET_XMID, RT_T_TRACE_
 RT_K_KINDS = 12
 KERNEL_KIND_NAMES = ["gemm_qkv", "gemm_o", "gemm_gate_up", "gemm_down", "gemm_context", "gemm_cond",
                      "attention", "attn_merge", "rmsnorm", "qkv_post", "lm_head", "misc"]
-RT_C_ATTN_SLOTS, RT_C_PAGE_POST, RT_C_PROMPT_ROWS = range(3)
+RT_C_ATTN_SLOTS, RT_C_PAGE_POST, RT_C_PROMPT_ROWS, RT_C_GEMM_COLS = range(4)
 STAGE_NAMES = ["condition", "draft", "draft_lm_head", "verify", "verify_lm_head", "accept", "context_append"]
 RT_PROF_STAGES = 7
 

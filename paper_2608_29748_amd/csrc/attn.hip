@@ -1270,14 +1270,6 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   for (int e = 0; e < PL; ++e) out[e] = Elem<T>::from_f32(num[e] * inv);
 }
 
-// One query tile per wave: 64-row blocks 8 waves with two LDS stages (64 KB at hd 128), or
-// three (96 KB) where every split holds long key
-// ranges: 8B batch-8 rounds 34.2 -> 32.6 us per layer (four stages 33.3), while the
-// short contexts of a 16-sequence serving batch ran 0.6 us slower with three; the kernel
-// that stages the q / k work's inputs keeps two (they take the third stage's room); 96-row
-// blocks 12 waves, three stages (96 KB; 15% faster than 4 waves of three tiles at the 14B
-// verify shape, where four stages measured no faster).  Results do not depend on the wave layout (the key-half
-// merge is written in explicit fused form).
 AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass) {
   AttnSlots r{splits, n_units * splits, n_units * splits};
   const int head = 256 / n_kv_heads;   // slots of one pass per KV head
@@ -1292,6 +1284,14 @@ AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass) {
   return r;
 }
 
+// One query tile per wave: 64-row blocks 8 waves with two LDS stages (64 KB at hd 128), or
+// three (96 KB) where every split holds long key
+// ranges: 8B batch-8 rounds 34.2 -> 32.6 us per layer (four stages 33.3), while the
+// short contexts of a 16-sequence serving batch ran 0.6 us slower with three; the kernel
+// that stages the q / k work's inputs keeps two (they take the third stage's room); 96-row
+// blocks 12 waves, three stages (96 KB; 15% faster than 4 waves of three tiles at the 14B
+// verify shape, where four stages measured no faster).  Results do not depend on the wave layout (the key-half
+// merge is written in explicit fused form).
 template <typename T>
 hipError_t attention_partials(const AttnArgs& a, hipStream_t s) {
   if (a.blocks && (a.splits != 1 || a.qkv || a.n_blocks < 1)) return hipErrorInvalidValue;

@@ -232,6 +232,44 @@ static bool page_post(const Plan& p, int rows, int rows_per_seq) {
   return rows_per_seq >= 5 && rows >= (p.esz == 2 ? 96 : 192);
 }
 
+// GEMMs on the skinny kernels: up to 32 rows, and 33..64 rows of bf16 operands with fewer than
+// 128 tiles of 96 columns and no slabs asked for.  The line was measured at 48 rows of the 4B
+// widths without slabs, on one projection below it and two above: q|k|v (6144 columns) 13.9 us
+// here against 14.7 on the mid-size kernel, gate|up (19456) 30.8 against 25.9, the LM head 150
+// against 131.
+static bool skinny_rows(bool bf16, bool af32, int kind, int M, int N) {
+  return M <= 32 || (M <= 64 && bf16 && !af32 && kind != EPI_PARTIAL && N < 128 * 96);
+}
+// k slabs of an o / down projection of more than 32 bf16 rows with room for `floats`
+static int resid_slabs(const Plan& p, int M, int Kp, size_t floats) {
+  GemmArgs g{};
+  g.Kp = Kp; g.partial_floats = floats;
+  g.e.kind = EPI_PARTIAL; g.e.M = M; g.e.N = p.d;
+  return gemm_mid_partial_slabs(g, false, kResidSplitsMax);
+}
+// Columns per workgroup of a target GEMM over M rows of a prompt pass (the LM head: a round)
+// on the mid-size kernel, 0 on another; a negative code for another kind.
+static int gemm_columns(const Plan& p, int kind, int M) {
+  GemmArgs g{};
+  g.Kp = kind == RT_K_GEMM_O ? p.Kp_q : kind == RT_K_GEMM_DOWN ? p.Kp_F : p.Kp_d;
+  g.ksplit = 1; g.partial_floats = kPartialFloats; g.e.M = M;
+  switch (kind) {
+    case RT_K_GEMM_QKV: g.e.kind = EPI_STORE_F32; g.e.N = p.qkvN; break;
+    case RT_K_GEMM_GATE_UP: g.e.kind = EPI_SWIGLU; g.e.N = 2 * p.F; break;
+    case RT_K_LM_HEAD: g.e.kind = EPI_ARGMAX; g.e.N = p.V; break;
+    case RT_K_GEMM_O:
+    case RT_K_GEMM_DOWN:
+      g.e.N = p.d;
+      if (M > 32) g.ksplit = resid_slabs(p, M, g.Kp, p.rpart_floats);
+      g.e.kind = g.ksplit > 1 || M <= 512 ? EPI_PARTIAL : EPI_RESID;
+      break;
+    default: return fail(RT_ERR_INVALID, "kernel kind %d has no column tile", kind);
+  }
+  // (the LM head of 33 rows and more always takes the mid-size kernel)
+  const bool skinny = kind == RT_K_LM_HEAD ? M <= 32 : skinny_rows(p.esz == 2, false, g.e.kind, M, g.e.N);
+  return p.esz != 2 || skinny ? 0 : gemm_mid_tile(g, false);
+}
+
 template <typename T, typename K>
 struct Engine : EngineBase {
   const char* tlayer(int l) const { return ws + p.t_layers + (size_t)l * p.layer_bytes; }
@@ -259,12 +297,8 @@ struct Engine : EngineBase {
     if (k_logical <= 0) k_logical = Kp;
     e.M = M;
     e.N = N;
-    // skinny up to 32 rows; 33..64 rows of bf16 operands where the mid-size kernel's tiles
-    // would leave more than half the chip idle (fewer than 128 of 96 columns: the 4B q|k|v,
-    // 6144 columns, 13.9 us against 14.7) and no slabs are asked for; the test hook (flags &
-    // 4) keeps 33..64 rows on the wide split-k path
-    const bool skinny = M <= 32 || (M <= 64 && sizeof(T) == 2 && !af32 && e.kind != EPI_PARTIAL && N < 128 * 96 &&
-                                    !(flags & 4));
+    // the test hook (flags & 4) keeps 33..64 rows on the wide split-k path
+    const bool skinny = M <= 32 || (skinny_rows(sizeof(T) == 2, af32, e.kind, M, N) && !(flags & 4));
     const int shape = skinny ? SHAPE_SKINNY : SHAPE_WIDE;
     const int KT = Kp / 32;
     int ks = 1;
@@ -319,7 +353,7 @@ struct Engine : EngineBase {
     T* cap;                      // packed capture buffer of the updated residual (null: none)
     int cap_k0;                  // column offset of this layer's slot in the capture
     const int32_t* prof_ctx;     // host copy of each sequence's context length (profiling only)
-    int defer;                   // o / down (<= 32 rows): k-slab partials, added by the next norm
+    int defer;                   // o / down (up to 32 rows; bf16 any rows): k-slab partials, added by the next norm
     int trace = -1;              // layer-trace record of this layer (-1: none)
     // prompt pass: its attention blocks and page items (then rows_per_seq, n_seqs, stride,
     // rb and pos0 are unused)
@@ -354,12 +388,8 @@ struct Engine : EngineBase {
     int ks = 1;
     if (defer) {
       ks = kResidSplits;
-      if (c.M > 32 && sizeof(T) == 2) {
-        GemmArgs g{};
-        g.Kp = Kp; g.partial_floats = c.blocks ? q.rpart_floats : (size_t)kResidSplitsMax * stride;
-        g.e.kind = EPI_PARTIAL; g.e.M = c.M; g.e.N = q.d;
-        ks = gemm_mid_partial_slabs(g, false, kResidSplitsMax);
-      }
+      if (c.M > 32 && sizeof(T) == 2)
+        ks = resid_slabs(q, c.M, Kp, c.blocks ? q.rpart_floats : (size_t)kResidSplitsMax * stride);
     }
     if (defer && (ks > 1 || c.M <= 512)) {
       e.kind = EPI_PARTIAL; e.out_f32 = pat<float>(q.rpart, q.s_rpart); e.ldo = q.d; e.part_stride = stride;
@@ -1637,6 +1667,10 @@ int rt_debug_choice(const rt_config* cfg, int32_t choice, int32_t n, int32_t arg
   if (choice == RT_C_PROMPT_ROWS) {
     if (n < 1 || n > p.bmax * (long long)p.T) return fail(RT_ERR_CAPACITY, "%d prompt rows", n);
     return prompt_pass_rows(p, n);
+  }
+  if (choice == RT_C_GEMM_COLS) {
+    if (n < 1 || n > p.Mrows) return fail(RT_ERR_CAPACITY, "%d rows outside [1, %d]", n, p.Mrows);
+    return gemm_columns(p, arg, n);
   }
   if (n < 1 || n > p.bmax) return fail(RT_ERR_CAPACITY, "%d sequences outside [1, %d]", n, p.bmax);
   if (arg != 1 && arg != p.bk) return fail(RT_ERR_INVALID, "rows per sequence must be 1 or the block size");

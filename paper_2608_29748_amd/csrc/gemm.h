@@ -126,6 +126,8 @@ int gemm_mid_store_slabs(const GemmArgs& a, bool a_f32);
 // count that fills the chip in the fewest rounds of the cost model (more than 512 rows: 1
 // where the direct epilogue is estimated faster than any slab count)
 int gemm_mid_partial_slabs(const GemmArgs& a, bool a_f32, int max_slabs);
+// Columns per workgroup that gemm_mid takes for these arguments (kind, M, N, Kp, ksplit)
+int gemm_mid_tile(const GemmArgs& a, bool a_f32);
 // Columns per workgroup of the mid-size kernel's argmax (LM head) launch over N columns
 // and M rows; it writes two partial keys per workgroup and row.
 int gemm_mid_cols(int N, int M);

@@ -334,8 +334,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 2)))
   }
 }
 
-// Columns per workgroup of the argmax (LM head) launch: 256 at 129..512 rows over a
-// large vocabulary (16 waves, 8% faster than 128 columns at the 14B shape), else 128 or 64
+// Columns per workgroup of the argmax (LM head) launch: 256 from 129 rows on over a large
+// vocabulary (one row tile: 16 waves, 8% faster than 128 columns at the 14B shape; several row
+// tiles: 8 waves, see mid_launch), else 128 or 64
 int gemm_mid_cols(int N, int M) {
   if (M > 128 && N / 256 >= 160) return 256;
   return N / 128 >= 160 ? 128 : 64;
@@ -482,6 +483,10 @@ int gemm_mid_store_slabs(const GemmArgs& a, bool a_f32) {
   if (g.e.kind == EPI_PARTIAL) g.e.kind = EPI_STORE_F32;
   if (g.e.M <= 32) return 1;
   return mid_plan(g, mid_rows(g.e.M), a_f32).ks;
+}
+
+int gemm_mid_tile(const GemmArgs& a, bool a_f32) {
+  return a.e.kind == EPI_ARGMAX ? gemm_mid_cols(a.e.N, a.e.M) : mid_plan(a, mid_rows(a.e.M), a_f32).NB;
 }
 
 // Fastest column tile of a GEMM of more than 512 rows with ks slabs (1: any tile).

@@ -62,3 +62,19 @@ def test_prompt_rows_per_pass(dtype, total, rows):
     for bad in (0, 4 * 8400 + 1):
         with pytest.raises(B.RetraceError):
             B.rt_debug_choice(c, B.RT_C_PROMPT_ROWS, bad)
+
+
+# columns per workgroup over the rows of a prompt pass (LM head: a round); 0: not the mid-size kernel
+@pytest.mark.parametrize("kind,rows,cols", [
+    (B.RT_K_GEMM_QKV, 32, 0), (B.RT_K_GEMM_QKV, 64, 0), (B.RT_K_GEMM_QKV, 4096, 192),
+    (B.RT_K_GEMM_GATE_UP, 32, 0), (B.RT_K_GEMM_GATE_UP, 48, 96), (B.RT_K_GEMM_GATE_UP, 128, 96),
+    (B.RT_K_GEMM_GATE_UP, 512, 160), (B.RT_K_GEMM_GATE_UP, 4096, 256), (B.RT_K_GEMM_O, 4096, 160),
+    (B.RT_K_GEMM_DOWN, 48, 64), (B.RT_K_GEMM_DOWN, 4096, 160), (B.RT_K_LM_HEAD, 32, 0), (B.RT_K_LM_HEAD, 33, 128),
+    (B.RT_K_LM_HEAD, 129, 256)])
+def test_gemm_columns(kind, rows, cols):
+    c = cfg(vocab=151936, mask_token_id=151935, max_batch=32)
+    assert B.rt_debug_choice(c, B.RT_C_GEMM_COLS, rows, kind) == cols
+    assert B.rt_debug_choice(cfg(dtype=B.RT_F32), B.RT_C_GEMM_COLS, min(rows, 4096), kind) == 0
+    for bad in ((0, kind), (4097, kind), (rows, B.RT_K_ATTENTION)):
+        with pytest.raises(B.RetraceError):
+            B.rt_debug_choice(c, B.RT_C_GEMM_COLS, *bad)
