@@ -81,12 +81,15 @@ __device__ __forceinline__ uint64_t wave_merge_top(uint64_t list, uint64_t batch
 // Stage 1: workgroup (c, row) keeps the top_k largest keys of logits c*kChunk .. of its row.
 // A lower bound of the top_k-th key comes first: every wave sorts its 64 lanes' maxima, of
 // which the top_k-th is reached by at least top_k logits, and the largest of the four waves'
-// bounds holds for the chunk.  The few logits that reach it (about 25 of 8192 random ones)
-// are collected in LDS and sorted by wave 0.  Where more than kCandMax logits tie or reach
-// the bound, every wave folds all its logits into a running top-64 instead (64 at a time).
+// bounds holds for the chunk.  The logits that reach it (of 8192 in random order about 74 at
+// top_k 20, 430 at 56 and 870, at most about 1500, at 64) are collected in LDS and sorted by
+// wave 0.  Where more than kCandMax tie or reach the bound, every wave folds all its logits
+// into a running top-64 instead (64 at a time).  A limit of 512 sent top_k above 55 there after
+// the bound was paid for (4 layers, 128 rows, round at top_k 64: 1660 us, 1329 with 2048; 56:
+// 1359 and 1271).
 // 128 rows of 151936 (78 MB of logits): 217 us with every 64 logits sorted, 39 us now; one
 // row 59 us and 12 us.
-constexpr int kCandMax = 512;
+constexpr int kCandMax = 2048;
 __global__ __launch_bounds__(kDistThreads) void topk_chunk_kernel(DistArgs a, uint64_t* cand, int n_chunks) {
   constexpr int NW = kDistThreads / 64, NV = kChunk / kDistThreads;   // values per thread
   __shared__ uint64_t lists[NW][64];
