@@ -383,8 +383,8 @@ static void mid_launch(const GemmArgs& a, int MB, int NB, dim3 grid, hipStream_t
   // 33..64 rows: 64-row tiles, 8 waves, six LDS stages.  The copies of the A rows (L2 hits)
   // and of the weights (HBM) share one in-order queue per compute unit and their times add
   // (measured per 1 KiB: about 8 ns and 38 ns with all units streaming), so half the A rows
-  // of the 128-row tile show: LM head 151936 x 2560 at 48 rows 147 -> 128 us (6.1 TB/s),
-  // 19456 x 2560 gate|up 30.4 -> 23.6 us, 2560 x 9728 down 15.4 (8 slabs) -> 11.7 (6).
+  // of the 128-row tile show: 48-row rounds of the 4B widths, LM head 150 -> 131 us; against
+  // the 32/64-column skinny kernel gate|up 30.8 -> 25.9 us, o / down 15.1 -> 10.5 (six slabs).
   if (MB == 64) {
     if constexpr (AF32) {
       if (NB == 64) RT_LAUNCH((gemm_mid_kernel<64, 64, 4, true, 8>), grid, dim3(512), 0, s, a);

@@ -22,8 +22,7 @@ inline size_t rup(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Prompt rows per prefill pass: the prompts of a call are laid end to end and run in passes
 // of at most this many rows (fewer where max_batch * max_seq_len is smaller).  At 4096 rows
-// the Qwen3-4B layer GEMMs fill the chip at 1.05-1.27 PFLOP/s, against 0.42-0.94 at 512
-// (o: 32 workgroups of 256 x 160); the activations of a pass take about 120 KB a row there.
+// the Qwen3-4B layer GEMMs fill the chip at 1.0-1.1 PFLOP/s, against 0.63-0.88 at 512; the activations of a pass take about 120 KB a row there.
 constexpr int kPrefillRows = 4096;
 constexpr int kPrefillRowsMin = 512;
 constexpr int kMaxTiles = 1 << 16;     // split-K arrival counters

@@ -87,8 +87,8 @@ __device__ __forceinline__ uint64_t wave_merge_top(uint64_t list, uint64_t batch
 // into a running top-64 instead (64 at a time).  A limit of 512 sent top_k above 55 there after
 // the bound was paid for (4 layers, 128 rows, round at top_k 64: 1660 us, 1329 with 2048; 56:
 // 1359 and 1271).
-// 128 rows of 151936 (78 MB of logits): 217 us with every 64 logits sorted, 39 us now; one
-// row 59 us and 12 us.
+// 128 rows of 151936 (78 MB of logits), top_k 20: 217 us with every 64 logits sorted, 32 us
+// now; one row 59 us and 11 us.
 constexpr int kCandMax = 2048;
 __global__ __launch_bounds__(kDistThreads) void topk_chunk_kernel(DistArgs a, uint64_t* cand, int n_chunks) {
   constexpr int NW = kDistThreads / 64, NV = kChunk / kDistThreads;   // values per thread
