@@ -17,6 +17,7 @@ struct AttnArgs {
   int n_q_heads, n_kv_heads, head_dim;
   int splits;                    // key-range splits per (seq, kv head, row block)
   int slots, fit;                // workgroups per KV head, and those of one pass of the chip: see attn_slots
+  int slots_each, fit_each;      // the same per unit, rounded down
   int row_blocks;                // row blocks of rb_rows (token, head) rows per sequence
   int rb_rows;                   // rows per block: 64, or 96 (bf16) when a sequence has 65..96 rows
   // Prompt passes (one key split): grid.z entry z works on the block
@@ -63,7 +64,7 @@ constexpr int kAttnBlockInts = 8;      // int32 per entry of AttnArgs::blocks
 // x 20 rows at head_dim 128 158 and 90), so a launch gets 256 / n_kv_heads slots a head where
 // that is two or more a unit.  Below two a unit it keeps the full count and the balanced plan
 // decides from the contexts how many to use.  Unbalanced launches take whole splits per unit.
-struct AttnSlots { int splits, slots, fit; };
+struct AttnSlots { int splits, slots, fit, slots_each, fit_each; };
 AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass);
 
 // Attention: attention_partials (per key split), then attention_merge (splits > 1).

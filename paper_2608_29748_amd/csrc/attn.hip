@@ -100,9 +100,13 @@ __device__ __forceinline__ SplitPlan attn_balanced_plan(const AttnArgs& a, int r
   const int nu = a.n_seqs * a.row_blocks;
   const int n = lane < nu ? attn_unit_chunks(a, lane, rbr) : 0;
   const int tot = __ockl_wfred_add_i32(n), mx = __ockl_wfred_max_i32(n);
-  // the smallest chunk count per split for which the splits fit `slots` (at least one a unit)
-  auto bound = [&](int slots) {
-    const int each = slots / nu;
+  // the smallest chunk count per split for which the splits fit one pass of the chip; with more
+  // slots than that, then for all of them.  One loop, the slots per unit from the host, and one
+  // call per kernel: with the search inlined twice in two calls a launch of eight sequences of
+  // 96..320 keys took 10.8 us, 10.0 so.
+  int q = 0, slots = a.fit, each = a.fit_each;
+#pragma unroll 1
+  for (;;) {
     int lo = max(1, max((tot + slots - 1) / slots, (mx + 63) / 64));
     int hi = max(lo, (mx + each - 1) / each);
     while (lo < hi) {
@@ -110,15 +114,13 @@ __device__ __forceinline__ SplitPlan attn_balanced_plan(const AttnArgs& a, int r
       if (__ockl_wfred_add_i32((n + mid - 1) / mid) <= slots) hi = mid;
       else lo = mid + 1;
     }
-    return lo;
-  };
-  int q = bound(a.fit);
-  if (a.slots > a.fit) {
     // more than one pass of the chip where that is shorter, as with one long context among
     // short ones: two passes, or, where a unit holds two workgroups (64 rows at head_dim 64,
     // 98 VGPRs and 74 KB), about 5/3 of a pass
-    const int q2 = bound(a.slots);
-    if (a.head_dim == 64 && rbr == 64 ? 5 * q2 < 3 * q : 2 * q2 < q) q = q2;
+    if (q == 0 || (a.head_dim == 64 && rbr == 64 ? 5 * lo < 3 * q : 2 * lo < q)) q = lo;
+    if (slots == a.slots) break;
+    slots = a.slots;
+    each = a.slots_each;
   }
   const int cnt = (n + q - 1) / q;
   return SplitPlan{cnt, __ockl_wfscan_add_i32(cnt, true), q};
@@ -136,13 +138,14 @@ __device__ __forceinline__ UnitInfo attn_unit(const AttnArgs& a, int unit) {
   return UnitInfo{s, unit % a.row_blocks, a.rows_per_seq, a.pos0[s * a.seq_stride], s * a.rows_per_seq};
 }
 // Work of the workgroup at (blockIdx.x, blockIdx.z): unit, split index within the unit
-// and the unit's split count; false for a slot the balanced plan leaves idle.
-__device__ __forceinline__ bool attn_slot_work(const AttnArgs& a, int rbr, int& unit, int& split, int& nsplit) {
+// and the unit's split count; false for a slot the balanced plan (p, of a balanced launch)
+// leaves idle.
+__device__ __forceinline__ bool attn_slot_work(const AttnArgs& a, const SplitPlan& p, int& unit, int& split,
+                                               int& nsplit) {
   if (!attn_balanced(a)) {
     unit = blockIdx.z; split = blockIdx.x; nsplit = a.splits;
     return true;
   }
-  const SplitPlan p = attn_balanced_plan(a, rbr);
   const int slot = blockIdx.z * a.splits + blockIdx.x;
   if (slot == 0 && blockIdx.y == 0 && threadIdx.x < 64) {   // hand the plan to the merge
     a.plan[threadIdx.x] = p.end - p.count;
@@ -224,7 +227,9 @@ __global__ __launch_bounds__(256) void attn_staged_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g4 = lane / 16, c16 = lane % 16;
   const int kvh = blockIdx.y;
   int unit, split, nsplit;
-  if (!attn_slot_work(a, kAttnRows, unit, split, nsplit)) return;
+  SplitPlan plan{};
+  if (attn_balanced(a)) plan = attn_balanced_plan(a, kAttnRows);
+  if (!attn_slot_work(a, plan, unit, split, nsplit)) return;
   const UnitInfo ui = attn_unit<true>(a, unit);
   const int s = ui.s, rb = ui.rb, nq = ui.nq, P = ui.P;
   const int G = a.n_q_heads / a.n_kv_heads;
@@ -599,13 +604,16 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
   SpanPlan sp{};
   unsigned long long seg_units = 0;   // spanning: units still to run
   const int slot = blockIdx.z * a.splits + blockIdx.x;
+  SplitPlan plan{};
+  const bool balanced = !PROMPT && attn_balanced(a);
+  if (balanced) plan = attn_balanced_plan(a, RBR);
   if constexpr (!FUSED && !PROMPT) {
-    if (a.span && attn_balanced(a)) {
+    if (a.span && balanced) {
       // span when its slots are shorter than the balanced plan's longest split by more
       // than the pipeline fill of a second segment (about three chunks, measured)
       sp = attn_span_plan(a, RBR);
       const int S = a.slots;
-      span = sp.ok && (a.span == 2 || (sp.total + S - 1) / S + 3 < attn_balanced_plan(a, RBR).q);
+      span = sp.ok && (a.span == 2 || (sp.total + S - 1) / S + 3 < plan.q);
     }
   }
   if (span) {
@@ -617,7 +625,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
     if (seg_units == 0) return;
   } else if (PROMPT) {
     unit = blockIdx.z;
-  } else if (!attn_slot_work(a, RBR, unit, split, nsplit)) {
+  } else if (!attn_slot_work(a, plan, unit, split, nsplit)) {
     return;
   }
   for (;;) {
@@ -1271,7 +1279,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 }
 
 AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass) {
-  AttnSlots r{splits, n_units * splits, n_units * splits};
+  AttnSlots r{splits, n_units * splits, n_units * splits, splits, splits};
   const int head = 256 / n_kv_heads;   // slots of one pass per KV head
   if (!one_pass || splits < 2 || r.slots <= head) return r;
   if (n_units < 2 || n_units > 64) {
@@ -1281,6 +1289,8 @@ AttnSlots attn_slots(int n_units, int n_kv_heads, int splits, bool one_pass) {
     r.fit = head > n_units ? head : n_units;
     if (head / n_units >= 2) r.slots = r.fit;
   }
+  r.slots_each = r.slots / n_units;
+  r.fit_each = r.fit / n_units;
   return r;
 }
 
@@ -1297,6 +1307,7 @@ hipError_t attention_partials(const AttnArgs& a, hipStream_t s) {
   if (a.blocks && (a.splits != 1 || a.qkv || a.n_blocks < 1)) return hipErrorInvalidValue;
   const int units = a.n_seqs * a.row_blocks;
   // a balanced launch of fewer slots than units * splits: one row of slots per head
+  if (!a.blocks && (a.fit_each < 1 || a.slots_each < 1)) return hipErrorInvalidValue;
   const bool cut = !a.blocks && a.slots != units * a.splits;
   if (cut && (a.splits < 2 || units < 2 || units > 64 || a.slots < units || a.slots > units * a.splits))
     return hipErrorInvalidValue;

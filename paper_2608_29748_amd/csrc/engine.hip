@@ -450,7 +450,8 @@ struct Engine : EngineBase {
     a.pos0 = c.pos0; a.seq_stride = c.stride; a.rows_per_seq = c.rows_per_seq;
     a.n_seqs = c.n_seqs; a.causal = c.causal; a.n_q_heads = q.Hq; a.n_kv_heads = q.Hkv; a.head_dim = q.hd;
     const AttnSlots sl = attn_slots(c.n_seqs * c.rb, q.Hkv, c.splits, attn_one_pass(q));
-    a.splits = sl.splits; a.slots = sl.slots; a.fit = sl.fit; a.row_blocks = c.rb; a.rb_rows = c.rb_rows;
+    a.splits = sl.splits; a.slots = sl.slots; a.fit = sl.fit;
+    a.slots_each = sl.slots_each; a.fit_each = sl.fit_each; a.row_blocks = c.rb; a.rb_rows = c.rb_rows;
     a.blocks = c.blocks; a.n_blocks = c.n_blocks;
     // batches whose attention never takes the q / k work (so the fused and separate forms,
     // compared by a test hook, share one plan) may span unit boundaries
